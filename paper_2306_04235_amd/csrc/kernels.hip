@@ -618,19 +618,48 @@ __global__ void k_fill_lp(LpTable tab, float* dst) {
   for (int i = threadIdx.x; i < tab.n; i += blockDim.x) dst[i] = tab.v[i];
 }
 
-// Arg-max of fp32 rows (smallest index among equal maxima), one wave per row.
-__global__ __launch_bounds__(256) void k_row_argmax(const float* __restrict__ z, int R, int V,
-                                                    unsigned long long* slots) {
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (r >= R) return;
+// Arg-max of fp32 rows (smallest index among equal maxima), one block per
+// row.  Bound by one CU's load path (128 KB per row of 32,000 logits): with
+// one wave per row each of 500 dependent iterations paid a memory round trip
+// (150 us for 16 rows of 32,000); 1024 threads with 8 loads of 16 bytes in
+// flight each take the row in one (V4: V a multiple of 4, rows 16-byte
+// aligned).
+template <bool V4>
+__global__ __launch_bounds__(1024) void k_row_argmax(const float* __restrict__ z, int V, unsigned long long* slots) {
+  __shared__ unsigned long long red[16];
+  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float* zr = z + (size_t)r * V;
   unsigned long long best = 0ull;
-  for (int v = lane; v < V; v += 64) {
-    const unsigned long long k = pack_argmax(z[(size_t)r * V + v], v);
+  auto take = [&](float x, int v) {
+    const unsigned long long k = pack_argmax(x, v);
     best = k > best ? k : best;
+  };
+  if constexpr (V4) {
+    const float4* z4 = reinterpret_cast<const float4*>(zr);
+    const int n4 = V / 4;
+    for (int i0 = tid; i0 < n4; i0 += 8 * 1024) {
+      float4 x[8];  // (indexes past the row repeat its last: the same key again)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = z4[min(i0 + 1024 * u, n4 - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int v = 4 * min(i0 + 1024 * u, n4 - 1);
+        take(x[u].x, v);
+        take(x[u].y, v + 1);
+        take(x[u].z, v + 2);
+        take(x[u].w, v + 3);
+      }
+    }
+  } else {
+    for (int v = tid; v < V; v += 1024) take(zr[v], v);
   }
   best = wave_max_u64(best);
-  if (lane == 0) slots[r] = best;
+  if (lane == 0) red[wave] = best;
+  __syncthreads();
+  if (wave == 0) {
+    best = wave_max_u64(red[lane & 15]);
+    if (lane == 0) slots[r] = best;
+  }
 }
 
 // The batch's source ids and lengths into the session, and the encoder
@@ -1626,7 +1655,10 @@ hipError_t launch_fill_lp(const LpTable& tab, float* dst, hipStream_t s) {
 
 hipError_t launch_row_argmax(const float* z, int R, int V, unsigned long long* slots, hipStream_t s) {
   if (R <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_row_argmax, dim3((R + 3) / 4), dim3(256), 0, s, z, R, V, slots);
+  if (V % 4 == 0 && reinterpret_cast<uintptr_t>(z) % 16 == 0)
+    hipLaunchKernelGGL(k_row_argmax<true>, dim3(R), dim3(1024), 0, s, z, V, slots);
+  else
+    hipLaunchKernelGGL(k_row_argmax<false>, dim3(R), dim3(1024), 0, s, z, V, slots);
   return hipGetLastError();
 }
 

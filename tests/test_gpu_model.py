@@ -152,6 +152,17 @@ def test_greedy_batch_above_gemv_limit(torch_dev):
     _greedy_check(torch, dev, DIVERSE, src, lens, 9)
 
 
+@pytest.mark.parametrize("V", [63, 4100, 32772])
+def test_row_argmax_widths(torch_dev, V):
+    """The arg-max of stored logits (9 rows): a vocabulary that is no multiple
+    of 4, one within a single round of 16-byte loads, and one just past it;
+    repeated embedding rows tie the maximum (the smallest index wins)."""
+    torch, dev = torch_dev
+    cfg = dataclasses.replace(DIVERSE, name=f"argmax-{V}", vocab=V, emb_distinct=41)
+    src, lens = G.make_sources(V, 9, (2, 9), seed=29, s_max=9)
+    _greedy_check(torch, dev, cfg, src, lens, 3)
+
+
 def test_diverse_model_output_depends_on_the_source(torch_dev):
     # the higher-variance test model's translations differ between sources
     torch, dev = torch_dev
