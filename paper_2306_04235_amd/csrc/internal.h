@@ -588,6 +588,69 @@ struct LayerDev {
   float sa_cqk = 0.f, sa_cpv = 0.f, ca_cqk = 0.f, ca_cpv = 0.f;
 };
 
+// Every decoder layer of one step in one launch (decode_rows.hip), for beam
+// search and for greedy search of 3 rows and more.  A layer's weights in
+// fragment order and its constants lie in one blob (kept by the session), at
+// these byte offsets; linear layers: 0 qkv, 1 o, 2 cq, 3 co, 4 w1, 5 w2.
+struct RowsOff {
+  unsigned ln[3];  // gain [d], then bias [d]: in front of qkv, cq and w1
+  unsigned c[6];   // scale [n], then bias [n]
+  unsigned n[6];   // output columns
+  unsigned w[6];   // weights
+  unsigned bytes;
+};
+__host__ __device__ constexpr RowsOff rows_off(int d, int F, bool w4) {
+  RowsOff o{};
+  const unsigned N[6] = {3u * d, (unsigned)d, (unsigned)d, (unsigned)d, (unsigned)F, (unsigned)d};
+  unsigned at = 64;  // the layer's scalars
+  for (int i = 0; i < 3; ++i) {
+    o.ln[i] = at;
+    at += 8u * d;
+  }
+  for (int i = 0; i < 6; ++i) {
+    o.n[i] = N[i];
+    o.c[i] = at;
+    at += 8u * N[i];
+  }
+  at = (at + 1023) / 1024 * 1024;
+  for (int i = 0; i < 6; ++i) {
+    o.w[i] = at;
+    at += N[i] * (i == 5 ? F : d) / (w4 ? 2 : 1);
+  }
+  o.bytes = (at + 1023) / 1024 * 1024;
+  return o;
+}
+struct RowsArgs {
+  const int8_t* blobs;      // layer l's blob is number index[l] (null: l)
+  const int32_t* index;
+  int n_layers, post, w4;
+  float eps;
+  LnDev fin_ln;             // the LayerNorm in front of the output projection
+  float inv_fin;
+  const int32_t* tok;       // [R] input tokens, embedded at position t; null: x holds the input rows
+  const int8_t* E;
+  const float* c_emb;
+  const float* pe;
+  int V;
+  float* x;                 // [R, d] input rows (tok null); the final residual rows on return
+  int8_t* out;              // [R, d] the output projection's int8 input
+  int R, W, RB;             // rows, rows per sentence, rows per block (set by the launcher)
+  int d, dh, h, F, T, S, t;
+  int8_t* kcache;           // layer l at + l * cache_stride: [R][T][d]
+  int8_t* vcache;
+  size_t cache_stride;
+  const int8_t* cross;      // layer l at + l * cross_stride: [B * S, 2d]
+  size_t cross_stride;
+  const int32_t* len;       // [B]
+  const int32_t* hist;      // [2][R][T] position -> cache row (beam), or null
+};
+constexpr int kRowsMaxLds = 160 * 1024;
+bool dec_rows_shape(int d, int dh, int F);
+size_t dec_rows_blob_bytes(int d, int F, bool w4);
+hipError_t launch_dec_rows_pack(const LayerDev& L, const LnDev& ln_self, bool post, bool w4, int8_t* blob,
+                                hipStream_t s);
+hipError_t launch_dec_rows(const RowsArgs& args, hipStream_t s);
+
 }  // namespace mnmt
 
 struct mnmt_model {
@@ -644,6 +707,9 @@ struct mnmt_session {
   int8_t* dec_u = nullptr;  // factorized embedding: the output projection's int8 input [R, emb_dim]
   int32_t* dec_part = nullptr;  // split-K partial sums [kMaxSplits][R][d] (launch_qgemm_split)
   std::vector<int8_t*> kcache, vcache;
+  int8_t* rows_blobs = nullptr;      // the row-wise decoder's layers (null: not used)
+  int32_t* rows_index = nullptr;     // blob number of each layer (null: its own)
+  bool rows_w4 = false;              // their weights are packed 4-bit codes
   int32_t* cur_tok = nullptr;
   int* step = nullptr;
   unsigned long long* slots = nullptr;

@@ -36,8 +36,46 @@ struct Plan {
   size_t cur_tok, step, slots, out_tok, finished, out_len, out_key, lp;
   size_t score, cand_score, cand_tok, tok_hist, par_hist, hist, fin_score, fin_len, fin_row, fin_count, done;
   size_t chain_err, enc_chain, beam_count, epoch, step_x64;
+  size_t rows_blobs, rows_index;  // the row-wise decoder's layers and their numbers (rows_bytes > 0)
+  size_t rows_bytes;
   size_t total;
 };
+
+// The linear layers of a decoder layer that run in the row-wise decoder.
+LinearDev LayerDev::*const kRowsLinears[] = {&LayerDev::qkv, &LayerDev::o,  &LayerDev::cq,
+                                             &LayerDev::co,  &LayerDev::w1, &LayerDev::w2};
+
+// The row-wise decoder reads packed 4-bit rows when every layer has them.
+bool rows_w4(const mnmt_model* m) {
+  for (const LayerDev& L : m->dec)
+    for (auto f : kRowsLinears)
+      if (!(L.*f).w4) return false;
+  return true;
+}
+
+// Number of each decoder layer's blob: layers that share parameters share it,
+// except that in post-LN models the LayerNorm in front of a layer is the
+// previous layer's, so there each layer has its own.
+std::vector<int32_t> rows_numbers(const mnmt_model* m) {
+  std::vector<int32_t> n(m->dec.size());
+  int32_t next = 0;
+  for (size_t l = 0; l < n.size(); ++l)
+    n[l] = m->dec_alias[l] >= 0 && !m->info.ln_post ? n[m->dec_alias[l]] : next++;
+  return n;
+}
+
+// Bytes of the row-wise decoder's blobs, or 0 for a session that does not
+// use them: models of other shapes, sessions of at most 2 rows (their step
+// kernels keep the weights row-major) and caches past the kernel's 31-bit
+// offsets.
+size_t rows_blobs_bytes(const mnmt_model* m, const mnmt_session_cfg& c) {
+  const size_t R = (size_t)c.max_batch * c.beam;
+  if (R < 3 || R * c.max_tgt_len * m->info.d_model >> 31 || !dec_rows_shape(m->info.d_model, m->dh, m->info.d_ffn))
+    return 0;
+  size_t n = 0;
+  for (int32_t i : rows_numbers(m)) n = (size_t)i + 1 > n ? i + 1 : n;
+  return n * dec_rows_blob_bytes(m->info.d_model, m->info.d_ffn, rows_w4(m));
+}
 
 int validate_cfg(const mnmt_model* m, const mnmt_session_cfg* c) {
   if (!m || !c) return set_error(MNMT_E_INVALID_ARG, "null model or session config");
@@ -131,6 +169,11 @@ Plan make_plan(const mnmt_model* m, const mnmt_session_cfg& c) {
   p.enc_chain = b.take(4 * 2 * (size_t)m->info.n_enc * kChainSlotWords);
   p.epoch = b.take(4);
   p.step_x64 = b.take(8 * 3 * Ld * 2 * d);
+  p.rows_bytes = rows_blobs_bytes(m, c);
+  if (p.rows_bytes) {
+    p.rows_blobs = b.take(p.rows_bytes);
+    p.rows_index = b.take(4 * Ld);
+  }
   p.total = (b.off + 255) / 256 * 256;
   return p;
 }
@@ -596,17 +639,69 @@ int run_decoder_layers(mnmt_session* S, int R, int W, bool beam, hipStream_t s, 
   return ln_rows(post ? last.ff_ln : m->dec_ln, m->inv_fin, false);
 }
 
-// Greedy step: layers, tied output projection with fused arg-max (batch <= 8)
-// or logits + row arg-max, then bookkeeping.  logits_out: optional [R, V].
-int greedy_step(mnmt_session* S, int R, int stop_at_eos, float* logits_out, hipStream_t s) {
+// The row-wise decoder runs every step whose session holds its blobs, except
+// 3 rows at width 512: a block's stream of 3.7 MB per layer then takes longer
+// than the launches it replaces (12 steps: 3.55 against 2.91 ms; 4 rows 3.72
+// against 3.83 ms, 8 rows 3.71 against 4.14 ms).
+bool rows_used(const mnmt_session* S, int R) { return S->rows_blobs && (R > 3 || S->m->info.d_model < 512); }
+
+// One decoder step for R rows in one launch (decode_rows.hip): position t,
+// input tokens cur_tok; ends as run_decoder_layers does.
+int run_decoder_rows(mnmt_session* S, int R, int W, bool beam, int t, hipStream_t s) {
   const mnmt_model* m = S->m;
-  int rc = run_decoder_layers(S, R, 1, false, s);
+  if (factored(m)) {
+    const int rc = embed_rows(S, S->cur_tok, R, 1, S->step, S->dec_x, s);
+    if (rc) return rc;
+  }
+  RowsArgs a{};
+  a.blobs = S->rows_blobs;
+  a.index = S->rows_index;
+  a.n_layers = (int)m->dec.size();
+  a.post = m->info.ln_post;
+  a.w4 = S->rows_w4;
+  a.eps = m->info.ln_eps;
+  a.fin_ln = a.post ? m->dec.back().ff_ln : m->dec_ln;
+  a.inv_fin = m->inv_fin;
+  a.tok = factored(m) ? nullptr : S->cur_tok;
+  a.E = m->E;
+  a.c_emb = m->c_emb;
+  a.pe = m->pe;
+  a.V = m->info.vocab;
+  a.x = S->dec_x;
+  a.out = S->dec_a;
+  a.R = R;
+  a.W = W;
+  a.d = m->info.d_model;
+  a.dh = m->dh;
+  a.h = m->info.n_heads;
+  a.F = m->info.d_ffn;
+  a.T = S->cfg.max_tgt_len;
+  a.S = S->S;
+  a.t = t;
+  a.kcache = S->kcache[0];
+  a.vcache = S->vcache[0];
+  a.cross = S->cross_kv[0];
+  if (m->dec.size() > 1) {  // equal buffers, taken in turn
+    a.cache_stride = S->kcache[1] - S->kcache[0];
+    a.cross_stride = S->cross_kv[1] - S->cross_kv[0];
+  }
+  a.len = S->len;
+  a.hist = beam ? S->beam.hist : nullptr;
+  LAUNCH(launch_dec_rows(a, s));
+  return MNMT_OK;
+}
+
+// Greedy step: layers, tied output projection with fused arg-max (batch <= 8,
+// operator by operator) or logits + row arg-max, then bookkeeping.  logits_out: optional [R, V].
+int greedy_step(mnmt_session* S, int R, int t, int stop_at_eos, float* logits_out, hipStream_t s) {
+  const mnmt_model* m = S->m;
+  int rc = rows_used(S, R) ? run_decoder_rows(S, R, 1, false, t, s) : run_decoder_layers(S, R, 1, false, s);
   if (rc) return rc;
   const int V = m->info.vocab;
   const int8_t* X;
   int K;
   if ((rc = logits_input(S, R, &X, &K, s))) return rc;
-  if (R <= 8) {
+  if (R <= 8 && !rows_used(S, R)) {
     EpiArgs e{EPI_LOGITS_ARGMAX, logits_out, V, 1.f, S->slots};
     LAUNCH(launch_qlinear(X, K, m->E, m->c_out, nullptr, R, K, V, e, s));
   } else {
@@ -1064,8 +1159,8 @@ int embed_step_input(mnmt_session* S, int R, hipStream_t s) {
 int greedy_step_any(mnmt_session* S, int R, int t, int stop_at_eos, float* logits_out, hipStream_t s,
                     bool fold = false, bool last = false, Chain* ch = nullptr) {
   if (step_path_used(S, R)) return greedy_step_v3(S, R, t, stop_at_eos, logits_out, s, fold, last, ch);
-  if (R <= 8 && !factored(S->m)) return greedy_step_fused(S, R, t, stop_at_eos, logits_out, s);
-  return greedy_step(S, R, stop_at_eos, logits_out, s);
+  if (R <= 8 && !factored(S->m) && !rows_used(S, R)) return greedy_step_fused(S, R, t, stop_at_eos, logits_out, s);
+  return greedy_step(S, R, t, stop_at_eos, logits_out, s);
 }
 
 // Step t of `steps`: from the second step on, the input rows come from the
@@ -1074,7 +1169,9 @@ int beam_step(mnmt_session* S, int R, int W, int t, int steps, hipStream_t s) {
   const mnmt_model* m = S->m;
   // factorized embeddings embed their rows in the decoder (the beam update
   // prepares rows of the model width only)
-  int rc = run_decoder_layers(S, R, W, true, s, t > 0 && !factored(m), t);
+  // (the row-wise decoder embeds its rows too)
+  int rc = rows_used(S, R) ? run_decoder_rows(S, R, W, true, t, s)
+                       : run_decoder_layers(S, R, W, true, s, t > 0 && !factored(m), t);
   if (rc) return rc;
   const int d = m->info.d_model, V = m->info.vocab;
   const int8_t* X;
@@ -1095,7 +1192,7 @@ int beam_step(mnmt_session* S, int R, int W, int t, int steps, hipStream_t s) {
   nx.d = d;
   nx.V = V;
   nx.P = m->info.max_pos;
-  nx.steps = factored(m) ? 0 : steps;
+  nx.steps = factored(m) || rows_used(S, R) ? 0 : steps;
   nx.do_ln = !m->info.ln_post;
   nx.g = L0.sa_ln.g;
   nx.b = L0.sa_ln.b;
@@ -1138,6 +1235,21 @@ int enqueue_search(mnmt_session* S, const mnmt_search_cfg& sc, hipStream_t s) {
       if ((rc = beam_step(S, R, sc.beam, t, sc.max_steps, s))) return rc;
   }
   return MNMT_OK;
+}
+
+// Write the row-wise decoder's blobs (each number's first layer).
+hipError_t pack_rows(const mnmt_model* m, int8_t* blobs, bool w4, hipStream_t s) {
+  const std::vector<int32_t> num = rows_numbers(m);
+  const size_t bytes = dec_rows_blob_bytes(m->info.d_model, m->info.d_ffn, w4);
+  hipError_t e = hipSuccess;
+  int32_t done = 0;
+  for (size_t l = 0; l < num.size() && e == hipSuccess; ++l) {
+    if (num[l] < done) continue;
+    const LnDev& ln = m->info.ln_post && l > 0 ? m->dec[l - 1].ff_ln : m->dec[l].sa_ln;
+    e = launch_dec_rows_pack(m->dec[l], ln, m->info.ln_post, w4, blobs + num[l] * bytes, s);
+    ++done;
+  }
+  return e;
 }
 
 int check_ptr(const void* p, const char* what) {
@@ -1307,10 +1419,20 @@ extern "C" int mnmt_session_create(const mnmt_model* model, const mnmt_session_c
   if (h == hipSuccess) h = hipMemsetAsync(S->epoch, 0, sizeof(unsigned), S->capture_stream);
   if (h == hipSuccess)
     h = hipMemsetAsync(S->step_x64, 0, 8 * 3 * (size_t)model->info.n_dec * 2 * d, S->capture_stream);
+  const std::vector<int32_t> numbers = rows_numbers(model);
+  if (h == hipSuccess && p.rows_bytes) {
+    S->rows_blobs = (int8_t*)at(p.rows_blobs);
+    S->rows_w4 = rows_w4(model);
+    h = pack_rows(model, S->rows_blobs, S->rows_w4, S->capture_stream);
+    for (size_t l = 0; l < numbers.size(); ++l)
+      if (numbers[l] != (int32_t)l) S->rows_index = (int32_t*)at(p.rows_index);
+    if (h == hipSuccess && S->rows_index)
+      h = hipMemcpyAsync(S->rows_index, numbers.data(), 4 * numbers.size(), hipMemcpyHostToDevice, S->capture_stream);
+  }
   if (h == hipSuccess) h = hipStreamSynchronize(S->capture_stream);
   if (h != hipSuccess) {
     mnmt_session_free(S);
-    return hip_error(h, "clearing the encoder accumulators");
+    return hip_error(h, "preparing the session's buffers");
   }
   *out = S;
   return MNMT_OK;

@@ -490,6 +490,49 @@ def test_postln_beam_above_64_rows(torch_dev):
 ODD_VOCAB = G.ModelConfig("odd-vocab", 64, 4, 128, 1, 1, 501, ln_post=0, seed=79, random_gamma=True, weight_std=0.1)
 
 
+# every width and feed-forward ratio of the row-wise decoder, int8 and 4-bit
+# weights, pre- and post-LN, heads of 16 to 64, shared layers
+ROWS = [
+    G.ModelConfig("rows-64-post", 64, 4, 128, 1, 2, 300, ln_post=1, seed=301, random_gamma=True, weight_std=0.1),
+    G.ModelConfig("rows-64-w4", 64, 2, 256, 1, 1, 301, ln_post=0, seed=302, random_gamma=True, weight_std=0.1, w_bits=4),
+    G.ModelConfig("rows-128", 128, 2, 512, 1, 2, 300, ln_post=0, seed=303, random_gamma=True, weight_std=0.1),
+    G.ModelConfig("rows-128-post-shared", 128, 8, 256, 1, 3, 300, ln_post=1, seed=304, weight_std=0.1, share_every=1),
+    G.ModelConfig("rows-256-w4", 256, 8, 512, 1, 2, 300, ln_post=0, seed=305, random_gamma=True, weight_std=0.1, w_bits=4),
+    G.ModelConfig("rows-256-shared", 256, 4, 1024, 1, 3, 300, ln_post=0, seed=306, weight_std=0.1, share_every=2),
+    G.ModelConfig("rows-384", 384, 6, 1536, 1, 1, 300, ln_post=0, seed=307, random_gamma=True, weight_std=0.05),
+    G.ModelConfig("rows-384-w4", 384, 8, 768, 1, 1, 300, ln_post=1, seed=308, weight_std=0.05, w_bits=4),
+    G.ModelConfig("rows-512", 512, 16, 1024, 1, 1, 300, ln_post=0, seed=309, random_gamma=True, weight_std=0.05),
+    G.ModelConfig("rows-512-w4", 512, 8, 2048, 1, 2, 300, ln_post=0, seed=310, weight_std=0.05, w_bits=4),
+]
+
+
+@pytest.mark.parametrize("cfg", ROWS, ids=lambda c: c.name)
+def test_row_wise_decoder_shapes(torch_dev, cfg):
+    """The row-wise decoder against the oracle: greedy with every step's logits
+    (5 rows; 67 source positions and 66 steps, past one group of 64 keys) and
+    beam search of width 3 (21 rows, histories that cross rows)."""
+    torch, dev = torch_dev
+    src, lens = G.make_sources(cfg.vocab, 5, [67, 64, 65, 1, 30], seed=311, s_max=67)
+    _greedy_check(torch, dev, cfg, src, lens, 66)
+    src, lens = G.make_sources(cfg.vocab, 7, (2, 24), seed=312, s_max=24)
+    _beam_check(torch, dev, cfg, src, lens, 3, 9, 0.6)
+
+
+@pytest.mark.parametrize("cfg,B,W,steps", [(ROWS[0], 530, 1, 3), (ROWS[2], 257, 1, 4), (ROWS[4], 100, 6, 5),
+                                           (ROWS[1], 1100, 1, 2), (ROWS[8], 90, 8, 2)],
+                         ids=lambda v: getattr(v, "name", str(v)))
+def test_row_wise_decoder_rows_per_block(torch_dev, cfg, B, W, steps):
+    """More than 256 rows: several rows per block (2, 3 and, past the four
+    rows of a 64-wide block, two rounds of blocks), a last block that is not
+    full, blocks that cross sentences, more (row, head) pairs than waves."""
+    torch, dev = torch_dev
+    src, lens = G.make_sources(cfg.vocab, B, (1, 9), seed=313, s_max=9)
+    if W == 1:
+        _greedy_check(torch, dev, cfg, src, lens, steps)
+    else:
+        _beam_check(torch, dev, cfg, src, lens, W, steps, 0.6)
+
+
 def test_small_models_beam(torch_dev):
     torch, dev = torch_dev
     for cfg in (SMALL_PRE, SMALL_POST, DIVERSE, ODD_VOCAB):  # odd vocabulary: the one-wave-per-row top-k
