@@ -46,6 +46,7 @@
 // sums in lane order, one fma per key for the attention context.
 #include "blocks.hpp"
 #include "internal.h"
+#include "rows.hpp"
 
 namespace mnmt {
 namespace {
@@ -65,7 +66,7 @@ struct RowsParams {
   RowsLds l;
 };
 
-// The scalars of a layer (RowsOff::hdr).
+// The scalars of a layer, first in its blob.
 struct RowsHdr {
   float sa_inv, ca_inv, ff_inv;  // 1 / input scale of qkv, cq, w1
   float sa_cqk, sa_cpv, ca_cqk, ca_cpv;
@@ -87,130 +88,17 @@ struct Shape {
   static constexpr int TD = 4 * KQ / WAVES, TQ = 3 * TD, TF = 4 * FQ / WAVES;  // tiles per wave
   static constexpr int kQkv = 0, kO = kQkv + TQ * NCH, kCq = kO + TD * NCH, kCo = kCq + TD * NCH,
                        kW1 = kCo + TD * NCH, kW2 = kW1 + TF * NCH, kEnd = kW2 + TD * NCH2;  // first batches
+  __host__ __device__ static constexpr BatchAt at(int b) {
+    return b < kO    ? batch_in(0, b - kQkv, NCH)
+           : b < kCq ? batch_in(1, b - kO, NCH)
+           : b < kCo ? batch_in(2, b - kCq, NCH)
+           : b < kW1 ? batch_in(3, b - kCo, NCH)
+           : b < kW2 ? batch_in(4, b - kW1, NCH)
+                     : batch_in(5, b - kW2, NCH2);
+  }
+  __host__ __device__ static constexpr RowsOff off(bool w4) { return rows_off(D, F, w4); }
   static_assert(KQ % C == 0 && FQ % C == 0 && 4 * KQ % WAVES == 0 && 4 * FQ % WAVES == 0 && kEnd % kRing == 0, "");
 };
-
-// Where a batch of the stream lies: linear layer (0..5), the wave's tile, the
-// tile's batch, slices per tile.
-struct BatchAt {
-  int lin, tile, ch, nch;
-};
-template <class S>
-__device__ constexpr BatchAt batch_at(int b) {
-  return b < S::kO    ? BatchAt{0, (b - S::kQkv) / S::NCH, (b - S::kQkv) % S::NCH, S::NCH}
-         : b < S::kCq ? BatchAt{1, (b - S::kO) / S::NCH, (b - S::kO) % S::NCH, S::NCH}
-         : b < S::kCo ? BatchAt{2, (b - S::kCq) / S::NCH, (b - S::kCq) % S::NCH, S::NCH}
-         : b < S::kW1 ? BatchAt{3, (b - S::kCo) / S::NCH, (b - S::kCo) % S::NCH, S::NCH}
-         : b < S::kW2 ? BatchAt{4, (b - S::kW1) / S::NCH, (b - S::kW1) % S::NCH, S::NCH}
-                      : BatchAt{5, (b - S::kW2) / S::NCH2, (b - S::kW2) % S::NCH2, S::NCH2};
-}
-
-// The wave's weights in flight: batch b in slot b % kRing, with the tile's
-// scale and bias of the lane's four columns beside its last batch.
-template <class S, bool W4>
-struct Ring {
-  WFrag<W4> f[S::kRing][S::C];
-  float4 sc[S::kRing], bi[S::kRing];
-};
-
-// A layer's blob as a buffer descriptor: a load's address is then the lane's
-// offset plus scalars, with no vector address arithmetic per load, and loads
-// past the blob return zero.
-typedef __amdgpu_buffer_rsrc_t Blob;
-template <class S, bool W4>
-__device__ __forceinline__ Blob blob_rsrc(const int8_t* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(base), 0, rows_off(S::D, S::F, W4).bytes, 0x00020000);
-}
-
-// Issue the loads of batch b (constant after unrolling; past the layer's last
-// batch: the next layer's) into its slot.
-template <class S, bool W4>
-__device__ __forceinline__ void issue(Ring<S, W4>& r, int b, Blob layer, Blob next, int wave, int lane) {
-  constexpr RowsOff O = rows_off(S::D, S::F, W4);
-  const Blob base = b < S::kEnd ? layer : next;
-  const int slot = b % S::kRing;
-  const BatchAt at = batch_at<S>(b < S::kEnd ? b : b - S::kEnd);
-  const int tile = wave + S::WAVES * at.tile;
-  const unsigned w = O.w[at.lin] + ((unsigned)(tile * at.nch + at.ch) * S::C) * (W4 ? 512u : 1024u);
-#pragma unroll
-  for (int u = 0; u < S::C; ++u) {
-    if constexpr (W4) {
-      const auto v = __builtin_amdgcn_raw_buffer_load_b64(base, 8 * lane, w + 512 * u, 0);
-      r.f[slot][u].p = make_uint2(v[0], v[1]);
-    } else {
-      const auto v = __builtin_amdgcn_raw_buffer_load_b128(base, 16 * lane, w + 1024 * u, 0);
-      r.f[slot][u].v = v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
-    }
-  }
-  if (at.ch == at.nch - 1) {
-    const unsigned c = O.c[at.lin] + 64 * tile, l = 16 * (lane >> 4);
-    const auto x = __builtin_amdgcn_raw_buffer_load_b128(base, l, c, 0);
-    const auto y = __builtin_amdgcn_raw_buffer_load_b128(base, l, c + 4 * O.n[at.lin], 0);
-    r.sc[slot] = make_float4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]), __uint_as_float(x[3]));
-    r.bi[slot] = make_float4(__uint_as_float(y[0]), __uint_as_float(y[1]), __uint_as_float(y[2]), __uint_as_float(y[3]));
-  }
-}
-
-// One linear layer: batches B0 .. B1 - 1 of the stream over the int8 rows in
-// LDS (the lane's row and chunk at arow).  The weights are the A operand, so
-// element i of lane l is column 4 (l / 16) + i of row l % 16: a lane finishes
-// four consecutive columns of one row.  epi(tile, acc, scale, bias).
-template <class S, bool W4, int B0, int B1, class Epi>
-__device__ __forceinline__ void linear(Ring<S, W4>& r, const int8_t* arow, Blob layer, Blob next, int wave,
-                                       int lane, Epi&& epi) {
-  v4i acc = {0, 0, 0, 0};
-#pragma unroll
-  for (int b = B0; b < B1; ++b) {
-    const int slot = b % S::kRing;
-    const BatchAt at = batch_at<S>(b);
-#pragma unroll
-    for (int u = 0; u < S::C; ++u)
-      acc = mfma16(r.f[slot][u].get(), *(const v4i*)(arow + 64 * (at.ch * S::C + u)), acc);
-    const float4 sc = r.sc[slot], bi = r.bi[slot];
-    issue(r, b + S::kRing, layer, next, wave, lane);
-    asm volatile("" ::: "memory");  // (the loads stay here: the compiler would sink them to their use)
-    if (at.ch == at.nch - 1) {
-      epi(wave + S::WAVES * at.tile, acc, sc, bi);
-      acc = v4i{0, 0, 0, 0};
-    }
-  }
-}
-
-// Four requantized codes of one row (columns col .. col + 3) as one word.
-template <bool RELU>
-__device__ __forceinline__ int pack_codes(const v4i acc, const float4 sc, const float4 bi) {
-  const float y[4] = {fmaf((float)acc[0], sc.x, bi.x), fmaf((float)acc[1], sc.y, bi.y),
-                      fmaf((float)acc[2], sc.z, bi.z), fmaf((float)acc[3], sc.w, bi.w)};
-  unsigned w = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    w |= (unsigned)(uint8_t)code_of(RELU ? fmaxf(y[i], 0.0f) : y[i]) << (8 * i);
-  return (int)w;
-}
-
-// LayerNorm (if do_ln) and quantization of the row x [d] in LDS by one wave,
-// into the int8 row q; the normalized row replaces x if `replace`.
-template <int KQ>
-__device__ __forceinline__ void norm_row(float* x, int do_ln, const float (&gj)[KQ], const float (&bj)[KQ], float eps,
-                                         float inv_s, bool replace, int8_t* q, int lane) {
-  constexpr int D = 64 * KQ;
-  float v[KQ];
-#pragma unroll
-  for (int j = 0; j < KQ; ++j) v[j] = x[lane + 64 * j];
-  if (do_ln) ln_row<KQ>(v, gj, bj, D, eps);
-#pragma unroll
-  for (int j = 0; j < KQ; ++j) {
-    q[lane + 64 * j] = code_of(v[j] * inv_s);
-    if (replace) x[lane + 64 * j] = v[j];
-  }
-}
-
-// the sum over the 4 lanes of a quad
-__device__ __forceinline__ int quad_sum(int v) {
-  v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, false);  // lanes 1 0 3 2
-  v += __builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, false);  // lanes 2 3 0 1
-  return v;
-}
 
 // Chunk c = lane % 4 (16 bytes) of the keys or values of positions t0 + 4 pp
 // + u, pp = lane / 4, of one head: SELF: position pos of the sentence's cache
@@ -303,18 +191,10 @@ __device__ __forceinline__ void attend_row(v4i (&kr)[4], const int8_t* kb, const
 #pragma unroll 1
   for (int t0 = 0; t0 < cached; t0 += 64) {
     if (t0 > 0) load_chunks<SELF>(v, vb, hist, T, ld, at + 16u * cc, cached, t0, pp);
+    int w[16];
+    transpose_chunks(v, w);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const unsigned a0 = __builtin_amdgcn_perm((unsigned)v[1][k], (unsigned)v[0][k], 0x05010400u);
-      const unsigned a1 = __builtin_amdgcn_perm((unsigned)v[1][k], (unsigned)v[0][k], 0x07030602u);
-      const unsigned b0 = __builtin_amdgcn_perm((unsigned)v[3][k], (unsigned)v[2][k], 0x05010400u);
-      const unsigned b1 = __builtin_amdgcn_perm((unsigned)v[3][k], (unsigned)v[2][k], 0x07030602u);
-      int* col = vt + (16 * c + 4 * k) * kVtStride + pp;
-      col[0] = (int)__builtin_amdgcn_perm(b0, a0, 0x05040100u);
-      col[kVtStride] = (int)__builtin_amdgcn_perm(b0, a0, 0x07060302u);
-      col[2 * kVtStride] = (int)__builtin_amdgcn_perm(b1, a1, 0x05040100u);
-      col[3 * kVtStride] = (int)__builtin_amdgcn_perm(b1, a1, 0x07060302u);
-    }
+    for (int k = 0; k < 16; ++k) vt[(16 * c + k) * kVtStride + pp] = w[k];
     wave_sync();  // the weights and the transposed values visible to the wave
     const int m = min(64, cached - t0);
     const float* pw = p + t0;
@@ -423,6 +303,7 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
     const int l16 = min(lane & 15, rows - 1), koff = 16 * (lane >> 4);
     const bool real = (lane & 15) < rows;  // the lane's row of a tile is one of the block's
     const int8_t* next = layer_base(min(l + 1, g.n_layers - 1));
+    const bool more = l + 1 < g.n_layers;
     const auto* hp = (const __attribute__((address_space(4))) float*)(uintptr_t)base;  // (scalar loads)
     const RowsHdr H{hp[0], hp[1], hp[2], hp[3], hp[4], hp[5], hp[6], hp[7], hp[8], hp[9]};
     int8_t* kc = g.kcache + l * g.cache_stride;
@@ -445,7 +326,7 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
       lds_barrier();
     };
     auto resid = [&](float gamma) {
-      return [=](int tile, const v4i acc, const float4 sc, const float4 bi) {
+      return [=](int, int tile, const v4i acc, const float4 sc, const float4 bi) {
         if (real) {
           float4* xp = reinterpret_cast<float4*>(xs + (lane & 15) * XS + 16 * tile + 4 * (lane >> 4));
           float4 x = *xp;
@@ -457,10 +338,10 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
         }
       };
     };
-    auto codes = [&](int tile, const v4i acc, const float4 sc, const float4 bi) {
+    auto codes = [&](int, int tile, const v4i acc, const float4 sc, const float4 bi) {
       if (real) *(int*)(act + (lane & 15) * QS + 16 * tile + 4 * (lane >> 4)) = pack_codes<false>(acc, sc, bi);
     };
-    auto relu_codes = [&](int tile, const v4i acc, const float4 sc, const float4 bi) {
+    auto relu_codes = [&](int, int tile, const v4i acc, const float4 sc, const float4 bi) {
       if (real) *(int*)(act + (lane & 15) * HS + 16 * tile + 4 * (lane >> 4)) = pack_codes<true>(acc, sc, bi);
     };
     const Blob lb = blob_rsrc<S, W4>(base), nb = blob_rsrc<S, W4>(next);
@@ -470,7 +351,7 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
     // self-attention: the cached keys of the wave's first unit go out before the LayerNorm and the projection
     if (wave < units) load_chunks<true>(kv, kc + (size_t)b0 * g.W * T * D, hs + i0 * hs_s, T, D, hd0 * dh + 16 * cc, t, 0, pp);
     norm(0, !(g.post && l == 0), H.sa_inv, g.post);
-    linear<S, W4, S::kQkv, S::kO>(ring, arow, lb, nb, wave, lane, codes);
+    linear<S, W4, S::kQkv, S::kO, 1, S::kEnd>(ring, arow, 0, lb, nb, more, wave, lane, codes);
     lds_barrier();
     for (int u = wave, i = i0, hd = hd0; u < units; u += WAVES) {
       const int8_t* qr = act + i * QS + hd * dh;
@@ -492,13 +373,13 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
       *(v4i*)(vc + o) = *(const v4i*)(act + r * QS + 2 * D + 16 * ch);
     }
     lds_barrier();
-    linear<S, W4, S::kO, S::kCq>(ring, arow, lb, nb, wave, lane, resid(H.sa_gamma));
+    linear<S, W4, S::kO, S::kCq, 1, S::kEnd>(ring, arow, 0, lb, nb, more, wave, lane, resid(H.sa_gamma));
     // cross-attention
     const int8_t* ck = ckv + (size_t)b0 * g.S * 2 * D + hd0 * dh;
     if (wave < units) load_chunks<false>(kv, ck, nullptr, 0, 2 * D, 16 * cc, n0, 0, pp);
     lds_barrier();
     norm(1, 1, H.ca_inv, g.post);
-    linear<S, W4, S::kCq, S::kCo>(ring, arow, lb, nb, wave, lane, codes);
+    linear<S, W4, S::kCq, S::kCo, 1, S::kEnd>(ring, arow, 0, lb, nb, more, wave, lane, codes);
     lds_barrier();
     int n = n0;
     for (int u = wave, i = i0, hd = hd0; u < units; u += WAVES) {
@@ -517,15 +398,15 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
       }
     }
     lds_barrier();
-    linear<S, W4, S::kCo, S::kW1>(ring, arow, lb, nb, wave, lane, resid(H.ca_gamma));
+    linear<S, W4, S::kCo, S::kW1, 1, S::kEnd>(ring, arow, 0, lb, nb, more, wave, lane, resid(H.ca_gamma));
     lds_barrier();
     // feed-forward
     norm(2, 1, H.ff_inv, g.post);
     const float4 ln_next = load_ln(next);
-    linear<S, W4, S::kW1, S::kW2>(ring, arow, lb, nb, wave, lane, relu_codes);
+    linear<S, W4, S::kW1, S::kW2, 1, S::kEnd>(ring, arow, 0, lb, nb, more, wave, lane, relu_codes);
     store_ln(ln_next);
     lds_barrier();
-    linear<S, W4, S::kW2, S::kEnd>(ring, hrow, lb, nb, wave, lane, resid(H.ff_gamma));
+    linear<S, W4, S::kW2, S::kEnd, 1, S::kEnd>(ring, hrow, 0, lb, nb, more, wave, lane, resid(H.ff_gamma));
     lds_barrier();
     base = next;
   }
@@ -584,41 +465,35 @@ hipError_t launch_kq(const RowsParams& P, int blocks, hipStream_t s) {
   return P.g.F == 2 * P.g.d ? launch_shape<KQ, 2 * KQ>(P, blocks, s) : launch_shape<KQ, 4 * KQ>(P, blocks, s);
 }
 
-// One layer's constants into its blob: array a of n floats (or the header's
-// scalars by value) by block a.
-constexpr int kRowsArrays = 18;
-struct RowsCopy {
-  RowsHdr hdr;
-  const float* src[kRowsArrays];
-  unsigned off[kRowsArrays];
-  int n[kRowsArrays];
-  int8_t* blob;
-};
-__global__ __launch_bounds__(256) void k_rows_consts(RowsCopy c) {
-  const int a = blockIdx.x;
-  float* dst = reinterpret_cast<float*>(c.blob + c.off[a]);
-  for (int i = threadIdx.x; i < c.n[a]; i += 256) dst[i] = c.src[a][i];
-  if (a == 0 && threadIdx.x == 0) *reinterpret_cast<RowsHdr*>(c.blob) = c.hdr;
-}
-
-// Fragment order of packed 4-bit rows: 8 bytes per lane, 512 per tile and slice.
-__global__ __launch_bounds__(256) void k_pack_fragments4(const uint8_t* __restrict__ W, int N, int K, size_t chunks,
-                                                         uint8_t* __restrict__ out) {
-  const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= chunks) return;
-  const int ks = K / 64, lane = (int)(c % 64);
-  const size_t j = (c / 64) % ks, t = c / (64 * (size_t)ks);
-  const size_t row = 16 * t + (lane & 15);
-  uint2 v = {0u, 0u};
-  if (row < (size_t)N) v = *(const uint2*)(W + row * (K / 2) + 32 * j + 8 * (lane >> 4));
-  *(uint2*)(out + 8 * c) = v;
-}
-
-hipError_t pack4(const uint8_t* W, int N, int K, uint8_t* out, hipStream_t s) {
-  const size_t chunks = frag_bytes(N, K) / 16;
-  if (chunks == 0) return hipErrorInvalidValue;
-  k_pack_fragments4<<<dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s>>>(W, N, K, chunks, out);
-  return hipGetLastError();
+// A blob from its parts, in one launch: block a < arrays copies a float array
+// (block 0 also the scalars), the others 256 fragment chunks each: a lane's 16
+// bytes (W4: 8) of tile t, slice j of a linear layer (launch_pack_fragments'
+// order).
+template <bool W4>
+__global__ __launch_bounds__(256) void k_rows_pack(RowsPack p) {
+  const int a = blockIdx.x, tid = threadIdx.x;
+  if (a < p.arrays) {
+    float* dst = reinterpret_cast<float*>(p.blob + p.off[a]);
+    for (int i = tid; i < p.n[a]; i += 256) dst[i] = p.src[a][i];
+    if (a == 0 && tid < 16) reinterpret_cast<float*>(p.blob)[tid] = p.hdr[tid];
+    return;
+  }
+  unsigned c = (unsigned)(a - p.arrays) * 256 + tid;
+  for (int i = 0; i < p.lins; ++i) {
+    const RowsPack::Lin& L = p.lin[i];
+    const unsigned ks = L.K / 64, chunks = L.N / 16 * ks * 64;
+    if (c >= chunks) {
+      c -= chunks;
+      continue;
+    }
+    const unsigned lane = c % 64, j = c / 64 % ks, t = c / (64 * ks);
+    const size_t at = (size_t)(16 * t + (lane & 15)) * L.K + 64 * j + 16 * (lane >> 4);  // code
+    if constexpr (W4)
+      *(uint2*)(p.blob + L.out + 8 * (size_t)c) = *(const uint2*)(L.W + at / 2);
+    else
+      *(int4*)(p.blob + L.out + 16 * (size_t)c) = *(const int4*)(L.W + at);
+    return;
+  }
 }
 
 }  // namespace
@@ -632,6 +507,24 @@ bool dec_rows_shape(int d, int dh, int F) {
 
 size_t dec_rows_blob_bytes(int d, int F, bool w4) { return rows_off(d, F, w4).bytes; }
 
+hipError_t launch_rows_pack(RowsPack& p, const LinearDev* const* lin, int n, const unsigned* c, const unsigned* cols,
+                            const unsigned* w, bool w4, hipStream_t s) {
+  size_t chunks = 0;
+  for (int i = 0; i < n; ++i)
+    if (lin[i]) {
+      rows_pack_add(p, lin[i]->scale, c[i], lin[i]->N);
+      rows_pack_add(p, lin[i]->bias, c[i] + 4 * cols[i], lin[i]->N);
+      p.lin[p.lins++] = RowsPack::Lin{w4 ? reinterpret_cast<const int8_t*>(lin[i]->w4) : lin[i]->w, lin[i]->N, lin[i]->K, w[i]};
+      chunks += (size_t)lin[i]->N * lin[i]->K / 16;
+    }
+  const dim3 grid(p.arrays + (unsigned)((chunks + 255) / 256));
+  if (w4)
+    k_rows_pack<true><<<grid, dim3(256), 0, s>>>(p);
+  else
+    k_rows_pack<false><<<grid, dim3(256), 0, s>>>(p);
+  return hipGetLastError();
+}
+
 // Reorder decoder layer L into its blob.  ln_self: the LayerNorm in front of
 // the layer's Q/K/V projection (post-LN: the previous layer's last).
 hipError_t launch_dec_rows_pack(const LayerDev& L, const LnDev& ln_self, bool post, bool w4, int8_t* blob,
@@ -641,31 +534,16 @@ hipError_t launch_dec_rows_pack(const LayerDev& L, const LnDev& ln_self, bool po
   const LinearDev* lin[6] = {&L.qkv, &L.o, &L.cq, &L.co, &L.w1, &L.w2};
   // post-LN: the rows in front of a sublayer are normalized by the sublayer before it
   const LnDev* ln[3] = {&ln_self, post ? &L.sa_ln : &L.ca_ln, post ? &L.ca_ln : &L.ff_ln};
-  RowsCopy c{};
-  c.hdr = RowsHdr{L.qkv.inv_in, L.cq.inv_in, L.w1.inv_in, L.sa_cqk,   L.sa_cpv,
-                  L.ca_cqk,     L.ca_cpv,    L.sa_gamma,  L.ca_gamma, L.ff_gamma};
-  c.blob = blob;
-  int k = 0;
-  auto add = [&](const float* src, unsigned off, int n) {
-    c.src[k] = src;
-    c.off[k] = off;
-    c.n[k++] = n;
-  };
+  RowsPack p{};
+  p.blob = blob;
+  const float hdr[10] = {L.qkv.inv_in, L.cq.inv_in, L.w1.inv_in, L.sa_cqk,   L.sa_cpv,
+                         L.ca_cqk,     L.ca_cpv,    L.sa_gamma,  L.ca_gamma, L.ff_gamma};
+  for (int i = 0; i < 10; ++i) p.hdr[i] = hdr[i];
   for (int i = 0; i < 3; ++i) {
-    add(ln[i]->g, O.ln[i], d);
-    add(ln[i]->b, O.ln[i] + 4 * d, d);
+    rows_pack_add(p, ln[i]->g, O.ln[i], d);
+    rows_pack_add(p, ln[i]->b, O.ln[i] + 4 * d, d);
   }
-  for (int i = 0; i < 6; ++i) {
-    add(lin[i]->scale, O.c[i], lin[i]->N);
-    add(lin[i]->bias, O.c[i] + 4 * O.n[i], lin[i]->N);
-  }
-  static_assert(kRowsArrays == 18, "6 LayerNorm and 12 linear-layer arrays");
-  k_rows_consts<<<dim3(kRowsArrays), dim3(256), 0, s>>>(c);
-  hipError_t e = hipGetLastError();
-  for (int i = 0; i < 6 && e == hipSuccess; ++i)
-    e = w4 ? pack4(lin[i]->w4, lin[i]->N, lin[i]->K, reinterpret_cast<uint8_t*>(blob + O.w[i]), s)
-           : launch_pack_fragments(lin[i]->w, lin[i]->N, lin[i]->K, blob + O.w[i], s);
-  return e;
+  return launch_rows_pack(p, lin, 6, O.c, O.n, O.w, w4, s);
 }
 
 namespace {

@@ -650,6 +650,82 @@ size_t dec_rows_blob_bytes(int d, int F, bool w4);
 hipError_t launch_dec_rows_pack(const LayerDev& L, const LnDev& ln_self, bool post, bool w4, int8_t* blob,
                                 hipStream_t s);
 hipError_t launch_dec_rows(const RowsArgs& args, hipStream_t s);
+// Filling a blob: its scalars, float arrays at byte offsets, and linear layers
+// (null: skipped) with constants at c[i], c[i] + 4 cols[i] and weights at w[i].
+struct RowsPack {
+  static constexpr int kMax = 18;
+  int8_t* blob;
+  float hdr[16];
+  const float* src[kMax];
+  unsigned off[kMax];
+  int n[kMax];
+  int arrays;
+  struct Lin {
+    const int8_t* W;  // [N, K] codes (N a multiple of 16) or packed 4-bit rows
+    int N, K;
+    unsigned out;
+  };
+  Lin lin[6];
+  int lins;
+};
+inline void rows_pack_add(RowsPack& p, const float* src, unsigned off, int n) {
+  p.src[p.arrays] = src;
+  p.off[p.arrays] = off;
+  p.n[p.arrays++] = n;
+}
+hipError_t launch_rows_pack(RowsPack& p, const LinearDev* const* lin, int n, const unsigned* c, const unsigned* cols,
+                            const unsigned* w, bool w4, hipStream_t s);
+
+// The encoder above 64 rows (encode_rows.hip): per layer the attention, then
+// the row-local rest in one launch from a blob at these offsets; linear
+// layers: 0 o, 1 w1, 2 w2, 3 the next layer's qkv.
+struct EncOff {
+  unsigned ln[2];  // gain [d], then bias [d]: in front of w1 and of what follows the layer
+  unsigned c[4], n[4], w[4], bytes;
+};
+__host__ __device__ constexpr EncOff enc_off(int d, int F, bool w4) {
+  EncOff o{};
+  const unsigned N[4] = {(unsigned)d, (unsigned)F, (unsigned)d, 3u * d};
+  unsigned at = 64;  // the scalars
+  for (int i = 0; i < 2; ++i) {
+    o.ln[i] = at;
+    at += 8u * d;
+  }
+  for (int i = 0; i < 4; ++i) {
+    o.n[i] = N[i];
+    o.c[i] = at;
+    at += 8u * N[i];
+  }
+  at = (at + 1023) / 1024 * 1024;
+  for (int i = 0; i < 4; ++i) {
+    o.w[i] = at;
+    at += N[i] * (i == 2 ? F : d) / (w4 ? 2 : 1);
+  }
+  o.bytes = (at + 1023) / 1024 * 1024;
+  return o;
+}
+struct EncRowsArgs {
+  const int8_t* blob;
+  int first, last, post, w4;
+  float eps;
+  const int32_t* tok;  // first: [R] source ids to embed (null: x holds the input rows)
+  const int8_t* E;
+  const float* c_emb;
+  const float* pe;
+  int V;
+  const int32_t* len;  // [R / S]
+  const int8_t* ctx;   // [R, d] attention context (not first)
+  float* x;            // [R, d] residual rows
+  int8_t* out;         // [R, 3d] Q/K/V codes; last: [R, d] the encoder's output
+  int R, S, RB;        // rows, rows per sentence, rows per block (set by the launcher)
+  int d, dh, F;
+};
+size_t enc_rows_blob_bytes(int d, int F, bool w4);
+hipError_t launch_enc_rows_pack(const LayerDev* L, const LinearDev* next, const LnDev& ln_ff, const LnDev& ln_next,
+                                float next_inv, int d, int F, bool w4, int8_t* blob, hipStream_t s);
+hipError_t launch_enc_rows(const EncRowsArgs& args, hipStream_t s);
+hipError_t launch_attn_enc_rows(const int8_t* qkv, const int32_t* len, int B, int S, int d, int h, float c_qk,
+                                float c_pv, int8_t* ctx, hipStream_t s);
 
 }  // namespace mnmt
 
@@ -710,6 +786,8 @@ struct mnmt_session {
   int8_t* rows_blobs = nullptr;      // the row-wise decoder's layers (null: not used)
   int32_t* rows_index = nullptr;     // blob number of each layer (null: its own)
   bool rows_w4 = false;              // their weights are packed 4-bit codes
+  int8_t* enc_blobs = nullptr;       // the row-wise encoder's passes (null: not used)
+  bool enc_w4 = false;
   int32_t* cur_tok = nullptr;
   int* step = nullptr;
   unsigned long long* slots = nullptr;

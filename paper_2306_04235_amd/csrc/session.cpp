@@ -38,6 +38,7 @@ struct Plan {
   size_t chain_err, enc_chain, beam_count, epoch, step_x64;
   size_t rows_blobs, rows_index;  // the row-wise decoder's layers and their numbers (rows_bytes > 0)
   size_t rows_bytes;
+  size_t enc_blobs, enc_blobs_bytes;  // the row-wise encoder's passes
   size_t total;
 };
 
@@ -75,6 +76,20 @@ size_t rows_blobs_bytes(const mnmt_model* m, const mnmt_session_cfg& c) {
   size_t n = 0;
   for (int32_t i : rows_numbers(m)) n = (size_t)i + 1 > n ? i + 1 : n;
   return n * dec_rows_blob_bytes(m->info.d_model, m->info.d_ffn, rows_w4(m));
+}
+
+// The row-wise encoder: packed 4-bit rows when every layer has them; blobs
+// for sessions that can hold more than 64 rows.
+bool enc_rows_w4(const mnmt_model* m) {
+  for (const LayerDev& L : m->enc)
+    for (const LinearDev* f : {&L.qkv, &L.o, &L.w1, &L.w2})
+      if (!f->w4) return false;
+  return true;
+}
+size_t enc_blobs_bytes(const mnmt_model* m, const mnmt_session_cfg& c) {
+  if ((size_t)c.max_batch * c.max_src_len <= kEncAccRows || !dec_rows_shape(m->info.d_model, m->dh, m->info.d_ffn))
+    return 0;
+  return (m->enc.size() + 1) * enc_rows_blob_bytes(m->info.d_model, m->info.d_ffn, enc_rows_w4(m));
 }
 
 int validate_cfg(const mnmt_model* m, const mnmt_session_cfg* c) {
@@ -174,6 +189,8 @@ Plan make_plan(const mnmt_model* m, const mnmt_session_cfg& c) {
     p.rows_blobs = b.take(p.rows_bytes);
     p.rows_index = b.take(4 * Ld);
   }
+  p.enc_blobs_bytes = enc_blobs_bytes(m, c);
+  if (p.enc_blobs_bytes) p.enc_blobs = b.take(p.enc_blobs_bytes);
   p.total = (b.off + 255) / 256 * 256;
   return p;
 }
@@ -438,6 +455,63 @@ int run_encoder_blocks(mnmt_session* S, hipStream_t s, Chain* ch = nullptr) {
   return MNMT_OK;
 }
 
+// The encoder in two launches per layer (encode_rows.hip).
+int run_encoder_rows(mnmt_session* S, hipStream_t s) {
+  const mnmt_model* m = S->m;
+  const int d = m->info.d_model, F = m->info.d_ffn, rows = S->B * S->S;
+  const size_t bytes = enc_rows_blob_bytes(d, F, S->enc_w4);
+  if (factored(m)) {
+    const int rc = embed_rows(S, S->src, rows, S->S, nullptr, S->enc_x, s);
+    if (rc) return rc;
+  }
+  EncRowsArgs g{};
+  g.post = m->info.ln_post;
+  g.w4 = S->enc_w4;
+  g.eps = m->info.ln_eps;
+  g.tok = factored(m) ? nullptr : S->src;
+  g.E = m->E;
+  g.c_emb = m->c_emb;
+  g.pe = m->pe;
+  g.V = m->info.vocab;
+  g.len = S->len;
+  g.ctx = S->enc_a;
+  g.x = S->enc_x;
+  g.R = rows;
+  g.S = S->S;
+  g.d = d;
+  g.dh = m->dh;
+  g.F = F;
+  for (size_t l = 0; l <= m->enc.size(); ++l) {  // pass l follows layer l - 1's attention
+    g.blob = S->enc_blobs + l * bytes;
+    g.first = l == 0;
+    g.last = l == m->enc.size();
+    g.out = g.last ? S->enc_out : S->enc_qkv;
+    LAUNCH(launch_enc_rows(g, s));
+    if (!g.last)
+      LAUNCH(launch_attn_enc_rows(S->enc_qkv, S->len, S->B, S->S, d, m->info.n_heads, m->enc[l].sa_cqk,
+                                  m->enc[l].sa_cpv, S->enc_a, s));
+  }
+  return MNMT_OK;
+}
+
+// Write the row-wise encoder's blobs.
+hipError_t pack_encoder(const mnmt_model* m, int8_t* blobs, bool w4, hipStream_t s) {
+  const int d = m->info.d_model, F = m->info.d_ffn;
+  const bool post = m->info.ln_post;
+  const size_t bytes = enc_rows_blob_bytes(d, F, w4), n = m->enc.size();
+  hipError_t e = hipSuccess;
+  for (size_t l = 0; l <= n && e == hipSuccess; ++l) {
+    const LayerDev* L = l ? &m->enc[l - 1] : nullptr;
+    const LayerDev* N = l < n ? &m->enc[l] : nullptr;
+    // post-LN: the layer's own LayerNorms follow its sublayers
+    const LnDev& ff = L ? (post ? L->sa_ln : L->ff_ln) : m->enc[0].ff_ln;
+    const LnDev& nx = post ? (L ? L->ff_ln : m->enc[0].sa_ln) : (N ? N->sa_ln : m->enc_ln);
+    e = launch_enc_rows_pack(L, N ? &N->qkv : nullptr, ff, nx, N ? N->qkv.inv_in : m->inv_enc, d, F, w4,
+                             blobs + l * bytes, s);
+  }
+  return e;
+}
+
 // Encoder over the session's current batch (rows = B * S, padded rows are
 // computed and ignored), then every decoder layer's cross keys/values.
 int run_encoder(mnmt_session* S, hipStream_t s) {
@@ -459,6 +533,12 @@ int run_encoder(mnmt_session* S, hipStream_t s) {
   }
   if (!factored(m) && qgemm_small_fits(rows, d) && qgemm_small_fits(rows, m->info.d_ffn))
     return run_encoder_small(S, s);
+  if (S->enc_blobs && rows > (int)kEncAccRows) {
+    int rc = run_encoder_rows(S, s);
+    for (size_t l = 0; l < m->dec.size() && !rc; ++l)
+      rc = qlin(m->dec[l].ckv, S->enc_out, rows, MNMT_EPI_I8, S->cross_kv[l], 1.f, s);
+    return rc;
+  }
   int rc0 = embed_rows(S, S->src, rows, S->S, nullptr, S->enc_x, s);
   if (rc0) return rc0;
   const LayerDev& L0 = m->enc[0];
@@ -1428,6 +1508,11 @@ extern "C" int mnmt_session_create(const mnmt_model* model, const mnmt_session_c
       if (numbers[l] != (int32_t)l) S->rows_index = (int32_t*)at(p.rows_index);
     if (h == hipSuccess && S->rows_index)
       h = hipMemcpyAsync(S->rows_index, numbers.data(), 4 * numbers.size(), hipMemcpyHostToDevice, S->capture_stream);
+  }
+  if (h == hipSuccess && p.enc_blobs_bytes) {
+    S->enc_blobs = (int8_t*)at(p.enc_blobs);
+    S->enc_w4 = enc_rows_w4(model);
+    h = pack_encoder(model, S->enc_blobs, S->enc_w4, S->capture_stream);
   }
   if (h == hipSuccess) h = hipStreamSynchronize(S->capture_stream);
   if (h != hipSuccess) {

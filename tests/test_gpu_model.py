@@ -493,16 +493,16 @@ ODD_VOCAB = G.ModelConfig("odd-vocab", 64, 4, 128, 1, 1, 501, ln_post=0, seed=79
 # every width and feed-forward ratio of the row-wise decoder, int8 and 4-bit
 # weights, pre- and post-LN, heads of 16 to 64, shared layers
 ROWS = [
-    G.ModelConfig("rows-64-post", 64, 4, 128, 1, 2, 300, ln_post=1, seed=301, random_gamma=True, weight_std=0.1),
-    G.ModelConfig("rows-64-w4", 64, 2, 256, 1, 1, 301, ln_post=0, seed=302, random_gamma=True, weight_std=0.1, w_bits=4),
-    G.ModelConfig("rows-128", 128, 2, 512, 1, 2, 300, ln_post=0, seed=303, random_gamma=True, weight_std=0.1),
-    G.ModelConfig("rows-128-post-shared", 128, 8, 256, 1, 3, 300, ln_post=1, seed=304, weight_std=0.1, share_every=1),
-    G.ModelConfig("rows-256-w4", 256, 8, 512, 1, 2, 300, ln_post=0, seed=305, random_gamma=True, weight_std=0.1, w_bits=4),
-    G.ModelConfig("rows-256-shared", 256, 4, 1024, 1, 3, 300, ln_post=0, seed=306, weight_std=0.1, share_every=2),
-    G.ModelConfig("rows-384", 384, 6, 1536, 1, 1, 300, ln_post=0, seed=307, random_gamma=True, weight_std=0.05),
-    G.ModelConfig("rows-384-w4", 384, 8, 768, 1, 1, 300, ln_post=1, seed=308, weight_std=0.05, w_bits=4),
-    G.ModelConfig("rows-512", 512, 16, 1024, 1, 1, 300, ln_post=0, seed=309, random_gamma=True, weight_std=0.05),
-    G.ModelConfig("rows-512-w4", 512, 8, 2048, 1, 2, 300, ln_post=0, seed=310, weight_std=0.05, w_bits=4),
+    G.ModelConfig("rows-64-post", 64, 4, 128, 2, 2, 300, ln_post=1, seed=301, random_gamma=True, weight_std=0.1),
+    G.ModelConfig("rows-64-w4", 64, 2, 256, 2, 1, 301, ln_post=0, seed=302, random_gamma=True, weight_std=0.1, w_bits=4),
+    G.ModelConfig("rows-128", 128, 2, 512, 2, 2, 300, ln_post=0, seed=303, random_gamma=True, weight_std=0.1),
+    G.ModelConfig("rows-128-post-shared", 128, 8, 256, 2, 3, 300, ln_post=1, seed=304, weight_std=0.1, share_every=1),
+    G.ModelConfig("rows-256-w4", 256, 8, 512, 2, 2, 300, ln_post=0, seed=305, random_gamma=True, weight_std=0.1, w_bits=4),
+    G.ModelConfig("rows-256-shared", 256, 4, 1024, 2, 3, 300, ln_post=0, seed=306, weight_std=0.1, share_every=2),
+    G.ModelConfig("rows-384", 384, 6, 1536, 2, 1, 300, ln_post=0, seed=307, random_gamma=True, weight_std=0.05),
+    G.ModelConfig("rows-384-w4", 384, 8, 768, 2, 1, 300, ln_post=1, seed=308, weight_std=0.05, w_bits=4),
+    G.ModelConfig("rows-512", 512, 16, 1024, 2, 1, 300, ln_post=0, seed=309, random_gamma=True, weight_std=0.05),
+    G.ModelConfig("rows-512-w4", 512, 8, 2048, 2, 2, 300, ln_post=0, seed=310, weight_std=0.05, w_bits=4),
 ]
 
 
@@ -531,6 +531,20 @@ def test_row_wise_decoder_rows_per_block(torch_dev, cfg, B, W, steps):
         _greedy_check(torch, dev, cfg, src, lens, steps)
     else:
         _beam_check(torch, dev, cfg, src, lens, W, steps, 0.6)
+
+
+@pytest.mark.parametrize("cfg,B,S", [(ROWS[0], 70, 64), (ROWS[4], 3, 130), (ROWS[2], 300, 30), (ROWS[9], 70, 60),
+                                     (ROWS[7], 2, 33)], ids=lambda v: getattr(v, "name", str(v)))
+def test_row_wise_encoder(torch_dev, cfg, B, S):
+    """The row-wise encoder against the oracle: 16 and 32 rows per block, more
+    than 8192 rows (two rounds), 64, 128 and 256 key classes, one block of a
+    sentence all padding, 66 rows."""
+    torch, dev = torch_dev
+    rng = np.random.Generator(np.random.PCG64(314))
+    lens = rng.integers(1, S + 1, B).astype(np.int32)
+    lens[0], lens[-1] = S, 1
+    src, lens = G.make_sources(cfg.vocab, B, lens, seed=315, s_max=S)
+    _greedy_check(torch, dev, cfg, src, lens, 2)
 
 
 def test_small_models_beam(torch_dev):
