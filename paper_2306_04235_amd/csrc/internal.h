@@ -45,6 +45,12 @@ hipError_t launch_gemm(const int8_t* X, int ldx, const int8_t* W, const float* s
 hipError_t launch_qlinear(const int8_t* X, int ldx, const int8_t* W, const float* scale, const float* bias,
                           int M, int K, int N, const EpiArgs& e, hipStream_t s, bool w4 = false);
 
+// The output projection of a batch (logits.hip): Y [M, N] fp32 = (X . W) *
+// scale; W [N, K] row-major or (frag) in fragment order (launch_pack_fragments).
+bool logits_rows_fit(int K, int N);
+hipError_t launch_logits_rows(const int8_t* X, int ldx, const int8_t* W, bool frag, const float* scale, int M, int K,
+                              int N, float* Y, hipStream_t s);
+
 // LayerNorm (optional) + quantization of rows of x [rows, d]:
 // do_ln: y = LN(x) with g, b, eps; else y = x.  q = quant(y, inv_s) if q;
 // x_out = y if x_out (post-LN writes the normalized row back).

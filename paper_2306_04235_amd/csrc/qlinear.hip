@@ -353,6 +353,8 @@ hipError_t launch_qlinear(const int8_t* X, int ldx, const int8_t* W, const float
                           int K, int N, const EpiArgs& e, hipStream_t s, bool w4) {
   if (M <= 0) return hipSuccess;
   if (w4 && (e.kind == EPI_LOGITS_ARGMAX || K % 64)) return hipErrorInvalidValue;
+  if (!w4 && e.kind == MNMT_EPI_LOGITS && M > 2 && logits_rows_fit(K, N) && e.ldo == N)
+    return launch_logits_rows(X, ldx, W, false, scale, M, K, N, static_cast<float*>(e.out), s);
   if (M <= 8)
     return w4 ? gemv_rows<true>(X, ldx, W, scale, bias, M, K, N, e, s)
               : gemv_rows<false>(X, ldx, W, scale, bias, M, K, N, e, s);

@@ -242,6 +242,20 @@ int logits_input(mnmt_session* S, int R, const int8_t** X, int* K, hipStream_t s
   return rc;
 }
 
+// The tied output projection of the int8 rows X [R, K] into fp32 logits z
+// [R, V], from the embedding's fragment-order copy where the wide kernel runs.
+int project_logits(const mnmt_session* S, const int8_t* X, int K, int R, float* z, hipStream_t s) {
+  const mnmt_model* m = S->m;
+  const int V = m->info.vocab;
+  if (m->E_frag && K == m->info.d_model && logits_rows_fit(K, V)) {
+    LAUNCH(launch_logits_rows(X, K, m->E_frag, true, m->c_out, R, K, V, z, s));
+  } else {
+    const EpiArgs e{MNMT_EPI_LOGITS, z, V, 1.f, nullptr};
+    LAUNCH(launch_qlinear(X, K, m->E, m->c_out, nullptr, R, K, V, e, s));
+  }
+  return MNMT_OK;
+}
+
 // Encoder for at most 64 rows (the batch-1 latency path): the embedding and
 // every LayerNorm run in the prologue of the matrix-core GEMM that consumes
 // them; per layer [LN + QKV] [attention] [W_o + residual] [LN + W1 + ReLU]
@@ -786,8 +800,7 @@ int greedy_step(mnmt_session* S, int R, int t, int stop_at_eos, float* logits_ou
     LAUNCH(launch_qlinear(X, K, m->E, m->c_out, nullptr, R, K, V, e, s));
   } else {
     float* z = logits_out ? logits_out : S->logits;
-    EpiArgs e{MNMT_EPI_LOGITS, z, V, 1.f, nullptr};
-    LAUNCH(launch_qlinear(X, K, m->E, m->c_out, nullptr, R, K, V, e, s));
+    if ((rc = project_logits(S, X, K, R, z, s))) return rc;
     LAUNCH(launch_row_argmax(z, R, V, S->slots, s));
   }
     LAUNCH(launch_greedy_commit(S->slots, R, S->cfg.max_tgt_len, S->cur_tok, S->out_tok, S->finished, S->out_len,
@@ -1257,8 +1270,7 @@ int beam_step(mnmt_session* S, int R, int W, int t, int steps, hipStream_t s) {
   const int8_t* X;
   int K;
   if ((rc = logits_input(S, R, &X, &K, s))) return rc;
-  EpiArgs e{MNMT_EPI_LOGITS, S->logits, V, 1.f, nullptr};
-  LAUNCH(launch_qlinear(X, K, m->E, m->c_out, nullptr, R, K, V, e, s));
+  if ((rc = project_logits(S, X, K, R, S->logits, s))) return rc;
   BeamState st = S->beam;
   st.t_host = t;  // the graph replays the steps in this order
   LAUNCH(launch_beam_topk(S->logits, st, S->step, s));

@@ -159,6 +159,28 @@ def test_qlinear_4bit_weights(torch_dev, M, K, N):
     assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
 
 
+@pytest.mark.parametrize("M,K,N", [(3, 64, 6145), (17, 128, 6417), (64, 256, 7001), (130, 256, 8000), (257, 384, 6273),
+                                   (330, 512, 6402), (5, 512, 32000)])
+def test_qlinear_wide_logits(torch_dev, M, K, N):
+    """The wide output projection: row ranges of 16 to 256 rows with a last
+    one that is not full, column blocks and 16-column tiles cut off by N."""
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+
+    rng = np.random.Generator(np.random.PCG64(61 * M + K + N))
+    X = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
+    W = rng.integers(-127, 128, size=(N, K)).astype(np.int8)
+    scale = rng.uniform(1e-5, 1e-3, size=N).astype(np.float32)
+    t = [torch.from_numpy(a).to(dev) for a in (X, W, scale)]
+    guard = torch.full((M * N + 64,), -7.0, device=dev)
+    out = guard[:M * N].view(M, N)
+    mnmt.mnmt_qlinear(t[0], t[1], t[2], None, mnmt.EPI_LOGITS, out=out)
+    torch.cuda.synchronize()
+    ref = oracle.qlinear(X, W, scale, None, oracle.EPI_LOGITS)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+    assert (guard[M * N:] == -7.0).all(), "stores past the output"
+
+
 def test_qlinear_4bit_rejects_argmax(torch_dev):
     torch, dev = torch_dev
     from paper_2306_04235_amd import mnmt

@@ -533,6 +533,16 @@ def test_row_wise_decoder_rows_per_block(torch_dev, cfg, B, W, steps):
         _beam_check(torch, dev, cfg, src, lens, W, steps, 0.6)
 
 
+@pytest.mark.parametrize("i,V,B", [(1, 6161, 3), (2, 6400, 20), (8, 8001, 9), (6, 6146, 290)])
+def test_wide_vocabulary_logits(torch_dev, i, V, B):
+    """The output projection from the fragment-order embedding (vocabularies
+    of more than 24 blocks of 256): widths 64 to 512, a last tile cut by V."""
+    torch, dev = torch_dev
+    cfg = dataclasses.replace(ROWS[i], name=f"{ROWS[i].name}-{V}", vocab=V)
+    src, lens = G.make_sources(V, B, (1, 6), seed=316, s_max=6)
+    _greedy_check(torch, dev, cfg, src, lens, 2)
+
+
 @pytest.mark.parametrize("cfg,B,S", [(ROWS[0], 70, 64), (ROWS[4], 3, 130), (ROWS[2], 300, 30), (ROWS[9], 70, 60),
                                      (ROWS[7], 2, 33)], ids=lambda v: getattr(v, "name", str(v)))
 def test_row_wise_encoder(torch_dev, cfg, B, S):
