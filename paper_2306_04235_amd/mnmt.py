@@ -102,14 +102,32 @@ def _check(rc: int, where: str):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    """A tensor's address (ctypes takes an int or None as void*; a c_void_p
+    object per argument costs more than the call's own checks)."""
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = None
 
 
 def _stream(stream=None):
-    import torch
+    """The stream's hipStream_t as an int: the given one, or the current one of
+    the current device."""
+    if stream is not None:
+        return stream.cuda_stream
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
 
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+        # torch.cuda.current_stream() builds a Stream object around this value
+        # (2 us of an 8 us call); the raw accessor is what it is built from
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and device is not None:
+            torch.cuda.current_stream()  # (the first call initializes the runtime)
+            _raw_stream = lambda: raw(device())  # noqa: E731
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    return _raw_stream()
 
 
 # ---- host-only entry points ---------------------------------------------------
@@ -131,37 +149,46 @@ def mnmt_fold_requant(s_in, s_w, b, s_out):
 
 
 # ---- device entry points ---------------------------------------------------------
+def _linear_out(X, M, N, epilogue):
+    """A new output tensor for the epilogue."""
+    import torch
+
+    if epilogue == EPI_ARGMAX:
+        return torch.zeros(M, dtype=torch.int64, device=X.device)  # packed (key, index) per row
+    if epilogue in (EPI_ARGMAX_PARTIAL, EPI_ARGMAX_PARTIAL_PACKED):
+        return torch.empty((M, argmax_partials(N)), dtype=torch.int64, device=X.device)
+    dt = torch.int32 if epilogue == EPI_I32 else torch.int8 if epilogue in (EPI_I8, EPI_I8_RELU) else torch.float32
+    return torch.empty((M, N), dtype=dt, device=X.device)
+
+
 def mnmt_qlinear(X, W, scale, bias, epilogue, gamma=1.0, out=None, stream=None, n_out=None):
     """Y = epilogue(X W^T) for int8 CUDA tensors X [M, K], W [N, K] (for
     EPI_ARGMAX_PARTIAL_PACKED, W is mnmt_pack_weights' output and n_out = N)."""
-    import torch
-
     M, K = X.shape
     N = W.shape[0] if n_out is None else int(n_out)
-    if out is None and epilogue == EPI_ARGMAX:
-        out = torch.zeros(M, dtype=torch.int64, device=X.device)  # packed (key, index) per row
-    elif out is None and epilogue in (EPI_ARGMAX_PARTIAL, EPI_ARGMAX_PARTIAL_PACKED):
-        out = torch.empty((M, argmax_partials(N)), dtype=torch.int64, device=X.device)
-    elif out is None:
-        dt = {EPI_I32: torch.int32, EPI_I8: torch.int8, EPI_I8_RELU: torch.int8}.get(epilogue, torch.float32)
-        out = torch.empty((M, N), dtype=dt, device=X.device)
-    _check(lib().mnmt_qlinear(_ptr(X), _ptr(W), _ptr(scale), _ptr(bias), M, K, N, epilogue, float(gamma),
-                              _ptr(out), _stream(stream)), "mnmt_qlinear")
+    if out is None:
+        out = _linear_out(X, M, N, epilogue)
+    rc = (_lib or lib()).mnmt_qlinear(_ptr(X), _ptr(W), _ptr(scale), _ptr(bias), M, K, N, epilogue, float(gamma),
+                                      _ptr(out), _stream(stream))
+    if rc:
+        _check(rc, "mnmt_qlinear")
     return out
 
 
 def mnmt_qlinear_w4(X, W4, scale, bias, epilogue, gamma=1.0, out=None, stream=None):
     """Y = epilogue(X W^T) for int8 CUDA tensor X [M, K] and W's packed 4-bit
     rows W4 uint8 [N, K / 2] (the model file's format)."""
-    import torch
-
     M, K = X.shape
     N = W4.shape[0]
     if out is None:
-        dt = {EPI_I32: torch.int32, EPI_I8: torch.int8, EPI_I8_RELU: torch.int8}.get(epilogue, torch.float32)
+        import torch
+
+        dt = torch.int32 if epilogue == EPI_I32 else torch.int8 if epilogue in (EPI_I8, EPI_I8_RELU) else torch.float32
         out = torch.empty((M, N), dtype=dt, device=X.device)
-    _check(lib().mnmt_qlinear_w4(_ptr(X), _ptr(W4), _ptr(scale), _ptr(bias), M, K, N, epilogue, float(gamma),
-                                 _ptr(out), _stream(stream)), "mnmt_qlinear_w4")
+    rc = (_lib or lib()).mnmt_qlinear_w4(_ptr(X), _ptr(W4), _ptr(scale), _ptr(bias), M, K, N, epilogue,
+                                         float(gamma), _ptr(out), _stream(stream))
+    if rc:
+        _check(rc, "mnmt_qlinear_w4")
     return out
 
 

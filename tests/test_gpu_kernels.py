@@ -181,6 +181,20 @@ def test_qlinear_wide_logits(torch_dev, M, K, N):
     assert (guard[M * N:] == -7.0).all(), "stores past the output"
 
 
+def test_binding_uses_the_current_stream(torch_dev):
+    """Calls without a stream go to torch's current one, whichever that is at
+    the time of the call."""
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+
+    side = torch.cuda.Stream()
+    for _ in range(2):
+        assert mnmt._stream() == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert mnmt._stream() == side.cuda_stream
+    assert mnmt._stream(side) == side.cuda_stream
+
+
 def test_qlinear_4bit_rejects_argmax(torch_dev):
     torch, dev = torch_dev
     from paper_2306_04235_amd import mnmt
