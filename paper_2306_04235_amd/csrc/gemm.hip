@@ -31,6 +31,11 @@ namespace {
 
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+// Output rows of any length: whole vectors at the alignment of an element (one
+// 16-byte access either way; the memory pipe splits the ones that need it).
+typedef v4i v4i_1 __attribute__((aligned(1)));
+typedef v4i v4i_4 __attribute__((aligned(4)));
+typedef v4f v4f_4 __attribute__((aligned(4)));
 
 constexpr int kBK = 64;            // K bytes per slab
 constexpr int kLdsRow = kBK + 16;  // padded LDS row (spreads rows over banks)
@@ -58,11 +63,13 @@ __device__ __forceinline__ float epi_value(int acc, float sc, float bi) {
 }
 
 // Writes one 32x32 accumulator fragment (columns nb .. nb + 31, this lane's
-// row m = row of lane l % 32).  FAST: the whole fragment is inside the output
-// and rows are 16-byte aligned, so no lane checks anything.
+// row m = row of lane l % 32).  FAST: the whole fragment is inside the output,
+// so no lane checks anything.  old: the residual's four words per g, if the
+// caller has them already.
 template <int EPI, bool FAST>
 __device__ __forceinline__ void store_fragment(const EpiArgs& e, const v16i& c, const float (&sc)[4][4],
-                                               const float (&bi)[4][4], int m, int nb, int h, int M, int N) {
+                                               const float (&bi)[4][4], int m, int nb, int h, int M, int N,
+                                               const v4f* old_rows = nullptr) {
   constexpr bool INT8_OUT = EPI == MNMT_EPI_I8 || EPI == MNMT_EPI_I8_RELU;
   if (INT8_OUT) {
     uint32_t w4[4];
@@ -83,7 +90,7 @@ __device__ __forceinline__ void store_fragment(const EpiArgs& e, const v16i& c, 
     if (!FAST) asm volatile("" : "+v"(n), "+v"(m));  // keeps the checks below inside this path
     int8_t* y = (int8_t*)e.out + (size_t)m * e.ldo + n;
     if (FAST) {
-      *(v4i*)y = v4i{(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
+      *(v4i_1*)y = v4i{(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
     } else if (m < M) {
 #pragma unroll
       for (int t = 0; t < 16; ++t)
@@ -99,7 +106,7 @@ __device__ __forceinline__ void store_fragment(const EpiArgs& e, const v16i& c, 
     if (EPI == MNMT_EPI_I32) {
       int* y = (int*)e.out + (size_t)m * e.ldo + n;
       if (FAST) {
-        *(v4i*)y = v4i{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+        *(v4i_4*)y = v4i{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
       } else {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -112,15 +119,15 @@ __device__ __forceinline__ void store_fragment(const EpiArgs& e, const v16i& c, 
       for (int t = 0; t < 4; ++t) v[t] = epi_value<EPI>(c[4 * g + t], sc[g][t], bi[g][t]);
       if (FAST) {
         if (EPI == MNMT_EPI_F32_RESID) {
-          const v4f old = *(const v4f*)y;
+          const v4f old = old_rows ? old_rows[g] : *(const v4f_4*)y;
 #pragma unroll
           for (int t = 0; t < 4; ++t) v[t] = fmaf(e.gamma, old[t], v[t]);
         }
-        *(v4f*)y = v;
+        *(v4f_4*)y = v;
       } else {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-          if (n + t < N) y[t] = EPI == MNMT_EPI_F32_RESID ? fmaf(e.gamma, y[t], v[t]) : v[t];
+          if (n + t < N) y[t] = EPI == MNMT_EPI_F32_RESID ? fmaf(e.gamma, old_rows ? old_rows[g][t] : y[t], v[t]) : v[t];
       }
     }
   }
@@ -142,7 +149,6 @@ __global__ __launch_bounds__(256) void k_gemm(const int8_t* __restrict__ X, int 
   static_assert(FN >= 1 && FM >= 1, "whole fragments");
   constexpr int CW = BN * (kBK / 16) / 256, CX = BM * (kBK / 16) / 256;  // 16-byte chunks per thread
   static_assert(CW >= 1 && CX >= 1, "every thread loads");
-  constexpr bool INT8_OUT = EPI == MNMT_EPI_I8 || EPI == MNMT_EPI_I8_RELU;
   __shared__ __attribute__((aligned(16))) int8_t Ws[2][BN * kLdsRow];
   __shared__ __attribute__((aligned(16))) int8_t Xs[2][BM * kLdsRow];
   __shared__ float sc_lds[BN], bi_lds[BN];  // the tile's epilogue constants
@@ -242,8 +248,6 @@ __global__ __launch_bounds__(256) void k_gemm(const int8_t* __restrict__ X, int 
   }
 
   // epilogue: whole fragments take the check-free path
-  const bool aligned = INT8_OUT ? (e.ldo % 16 == 0 && (reinterpret_cast<uintptr_t>(e.out) & 15) == 0)
-                                : (e.ldo % 4 == 0 && (reinterpret_cast<uintptr_t>(e.out) & 15) == 0);
 #pragma unroll
   for (int j = 0; j < FN; ++j) {
     const int cb = wn * TN + 32 * j;  // fragment's first column within the tile
@@ -261,11 +265,148 @@ __global__ __launch_bounds__(256) void k_gemm(const int8_t* __restrict__ X, int 
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const int mb = m0 + wm * TM + 32 * i;
-      const bool fast = aligned && n0 + cb + 32 <= N && mb + 32 <= M;  // uniform over the wave
+      const bool fast = n0 + cb + 32 <= N && mb + 32 <= M;  // uniform over the wave
       if (fast)
         store_fragment<EPI, true>(e, acc[j][i], sc, bi, mb + l32, n0 + cb, h, M, N);
       else
         store_fragment<EPI, false>(e, acc[j][i], sc, bi, mb + l32, n0 + cb, h, M, N);
+    }
+  }
+}
+
+// One BT x BT tile per block with K taken in chunks of KC bytes.  Bound by
+// latency up to a few blocks per CU: with 64-byte slabs every slab waits for
+// the previous one's loads (512 x 512 x 2048: eight dependent round trips);
+// here a block issues the loads of a whole chunk at once, its epilogue
+// constants and residual rows behind them, so K <= 512 is one round trip in 64
+// x 64 tiles.  A longer K loads its next chunk while this one is multiplied.
+// Loads past the end of K repeat its last 16 codes (never multiplied).
+// Against the slabs: 512 x 512 x 2048 to int8 4.6 -> 3.7 us, 512 x 2048 x 512
+// to int32 9.5 -> 7.3 us, 700 x 2048 x 512 with residual 12.4 -> 8.2 us.
+// 128 x 128 tiles in chunks of 128 keep two blocks per CU where there are
+// tiles for that (3000 x 1536 x 5001 45.8 -> 37.4 us; in chunks of 256 40.6).
+//
+// Rows of any length and alignment take vector stores (store_fragment): rows
+// that are no multiple of 16 bytes were written byte by byte (3000 x 512 x
+// 5001 58 us, 2100 x 256 x 30007 192 us; now 18.4 and 41).
+template <int BT, int KC, int EPI, bool W4>
+__global__ __launch_bounds__(256) void k_gemm_chunk(const int8_t* X, int ldx, const int8_t* W, int M, int K, int N,
+                                                    const float* scale, const float* bias, EpiArgs e, int tiles_m,
+                                                    int tiles, int kb) {
+  constexpr int ROW = KC + 16, CPR = KC / 16, CL = BT * CPR / 256;  // padded LDS row, 16-byte chunks
+  constexpr int F = BT / 64;  // the wave's fragments: F x F of 32 x 32
+  static_assert(KC % 64 == 0 && BT * CPR % 256 == 0, "whole loads");
+  __shared__ __attribute__((aligned(16))) int8_t Ws[BT * ROW];
+  __shared__ __attribute__((aligned(16))) int8_t Xs[BT * ROW];
+  __shared__ __attribute__((aligned(16))) float sc_lds[BT], bi_lds[BT];
+  const int b = blockIdx.x;
+  const int per = (tiles + kXcds - 1) / kXcds;
+  const int tile = (b % kXcds) * per + b / kXcds;
+  if (tile >= tiles) return;  // the grid is rounded up to whole XCD ranges
+  const int m0 = (tile % tiles_m) * BT, n0 = (tile / tiles_m) * BT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  const int cb = BT / 2 * (wave >> 1), rb = BT / 2 * (wave & 1);  // the wave's columns and rows within the tile
+  const int kbeg = blockIdx.y * kb;
+  if (gridDim.y > 1) e.out = (int*)e.out + (size_t)blockIdx.y * M * e.ldo;
+
+  constexpr int WDIV = W4 ? 2 : 1;
+  WFrag<W4> rw[CL];
+  v4i rx[CL];
+  auto gload = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < CL; ++i) {
+      const int c = tid + 256 * i, r = c / CPR, k = kbeg + min(k0 + 16 * (c % CPR), kb - 16);
+      const int8_t* w = W + ((uint32_t)min(n0 + r, N - 1) * (uint32_t)(K / WDIV) + (uint32_t)(k / WDIV));
+      if constexpr (W4)
+        rw[i].p = *(const uint2*)w;
+      else
+        rw[i].v = *(const v4i*)w;
+      rx[i] = *(const v4i*)(X + ((uint32_t)min(m0 + r, M - 1) * (uint32_t)ldx + (uint32_t)k));
+    }
+  };
+  gload(0);
+  float rc = 0.0f;  // scale, then bias: 2 BT <= 256 threads
+  if (EPI != MNMT_EPI_I32 && tid < 2 * BT) {
+    const int n = min(n0 + tid % BT, N - 1);
+    rc = tid < BT ? scale[n] : EPI == MNMT_EPI_LOGITS ? 0.0f : bias[n];
+  }
+  // the residual rows of a 64-wide tile (in a larger one they take the
+  // accumulators' registers: 28 -> 54 us for 1500 x 2048 x 3000)
+  v4f old[4];
+  if (EPI == MNMT_EPI_F32_RESID && BT == 64) {
+    const float* y = (const float*)e.out + (size_t)min(m0 + rb + l32, M - 1) * e.ldo;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = n0 + cb + 8 * g + 4 * h;
+      if (n0 + cb + 32 <= N) {
+        old[g] = *(const v4f_4*)(y + n);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) old[g][t] = y[min(n + t, N - 1)];
+      }
+    }
+  }
+  asm volatile("" ::: "memory");  // (the loads stay here)
+  v16i acc[F][F];
+#pragma unroll
+  for (int j = 0; j < F; ++j)
+#pragma unroll
+    for (int i = 0; i < F; ++i) acc[j][i] = v16i{};
+  for (int k0 = 0;; k0 += KC) {
+#pragma unroll
+    for (int i = 0; i < CL; ++i) {
+      const int c = tid + 256 * i, at = (c / CPR) * ROW + 16 * (c % CPR);
+      *(v4i*)(Ws + at) = rw[i].get();
+      *(v4i*)(Xs + at) = rx[i];
+    }
+    if (EPI != MNMT_EPI_I32 && k0 == 0 && tid < 2 * BT) (tid < BT ? sc_lds : bi_lds)[tid % BT] = rc;
+    lds_barrier();
+    const bool more = k0 + KC < kb;
+    if (more) gload(k0 + KC);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int kk = 0; kk < KC; kk += 64) {
+      if (k0 + kk < kb) {
+#pragma unroll
+        for (int q = 0; q < 64; q += 32) {
+          v4i a[F], x[F];
+#pragma unroll
+          for (int j = 0; j < F; ++j) a[j] = *(const v4i*)(Ws + (cb + 32 * j + l32) * ROW + kk + q + 16 * h);
+#pragma unroll
+          for (int i = 0; i < F; ++i) x[i] = *(const v4i*)(Xs + (rb + 32 * i + l32) * ROW + kk + q + 16 * h);
+#pragma unroll
+          for (int j = 0; j < F; ++j)
+#pragma unroll
+            for (int i = 0; i < F; ++i) acc[j][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[j], x[i], acc[j][i], 0, 0, 0);
+        }
+      }
+    }
+    if (!more) break;
+    lds_barrier();  // every wave is done with the chunk
+  }
+#pragma unroll
+  for (int j = 0; j < F; ++j) {
+    const int c0 = cb + 32 * j;
+    float sc[4][4], bi[4][4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const v4f s4 = *(const v4f*)(sc_lds + c0 + 8 * g + 4 * h);
+      const v4f b4 = *(const v4f*)(bi_lds + c0 + 8 * g + 4 * h);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        sc[g][t] = EPI == MNMT_EPI_I32 ? 0.0f : s4[t];
+        bi[g][t] = EPI == MNMT_EPI_I32 ? 0.0f : b4[t];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < F; ++i) {
+      const int r0 = m0 + rb + 32 * i;
+      const v4f* pre = EPI == MNMT_EPI_F32_RESID && BT == 64 ? old : nullptr;
+      if (n0 + c0 + 32 <= N && r0 + 32 <= M)  // the whole fragment, uniform over the wave
+        store_fragment<EPI, true>(e, acc[j][i], sc, bi, r0 + l32, n0 + c0, h, M, N, pre);
+      else
+        store_fragment<EPI, false>(e, acc[j][i], sc, bi, r0 + l32, n0 + c0, h, M, N, pre);
     }
   }
 }
@@ -431,6 +572,38 @@ hipError_t launch_cfg(const int8_t* X, int ldx, const int8_t* W, const float* sc
   }
 #undef MNMT_GEMM
   return hipGetLastError();
+}
+
+template <int BT, int KC, bool W4>
+hipError_t launch_chunk_kc(const int8_t* X, int ldx, const int8_t* W, const float* scale, const float* bias, int M,
+                           int K, int N, const EpiArgs& e, hipStream_t s, int splits) {
+  const int tiles_m = (M + BT - 1) / BT, tiles = tiles_m * ((N + BT - 1) / BT);
+  const int grid = (tiles + kXcds - 1) / kXcds * kXcds;
+#define MNMT_GEMM(EPI)                                                                                             \
+  hipLaunchKernelGGL((k_gemm_chunk<BT, KC, EPI, W4>), dim3(grid, splits), dim3(256), 0, s, X, ldx, W, M, K, N, scale, \
+                     bias, e, tiles_m, tiles, K / splits)
+  switch (e.kind) {
+    case MNMT_EPI_I32: MNMT_GEMM(MNMT_EPI_I32); break;
+    case MNMT_EPI_I8: MNMT_GEMM(MNMT_EPI_I8); break;
+    case MNMT_EPI_I8_RELU: MNMT_GEMM(MNMT_EPI_I8_RELU); break;
+    case MNMT_EPI_F32: MNMT_GEMM(MNMT_EPI_F32); break;
+    case MNMT_EPI_F32_RESID: MNMT_GEMM(MNMT_EPI_F32_RESID); break;
+    case MNMT_EPI_LOGITS: MNMT_GEMM(MNMT_EPI_LOGITS); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef MNMT_GEMM
+  return hipGetLastError();
+}
+
+// K in the fewest chunks of at most 512 bytes, evenly filled.
+template <bool W4>
+hipError_t launch_chunk(const int8_t* X, int ldx, const int8_t* W, const float* scale, const float* bias, int M, int K,
+                        int N, const EpiArgs& e, hipStream_t s, int splits = 1) {
+  const int kb = K / splits, kc = kb / ((kb + 511) / 512);
+  if (kc <= 128) return launch_chunk_kc<64, 128, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
+  if (kc <= 256) return launch_chunk_kc<64, 256, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
+  if (kc <= 384) return launch_chunk_kc<64, 384, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
+  return launch_chunk_kc<64, 512, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
 }
 
 template <int BN, int BM, int KC, int KCN, bool W4>
@@ -717,29 +890,42 @@ hipError_t launch_tiled(const int8_t* X, int ldx, const int8_t* W, const float* 
       default: break;
     }
   }
+  // (K loops of many slabs hide the round trips themselves, and at 256 x 128
+  // each byte in LDS feeds the most products: 4090 x 1984 x 30000 304 against
+  // 336 us in 128 x 128 chunk tiles; wide outputs of a short K are bound by
+  // their stores: 2100 x 384 x 31003 to int32 94 against 97 us)
   constexpr long kFill = 512;
-  if (tiles(256, 128) >= kFill) return launch_cfg<256, 128, 2, 2, W4>(X, ldx, W, scale, bias, M, K, N, e, s);
-  if (tiles(128, 128) >= kFill) return launch_cfg<128, 128, 2, 2, W4>(X, ldx, W, scale, bias, M, K, N, e, s);
-  if (tiles(128, 64) >= kFill) return launch_cfg<128, 64, 2, 2, W4>(X, ldx, W, scale, bias, M, K, N, e, s);
-  return launch_cfg<64, 64, 2, 2, W4>(X, ldx, W, scale, bias, M, K, N, e, s);
+  const bool int8_out = e.kind == MNMT_EPI_I8 || e.kind == MNMT_EPI_I8_RELU, resid = e.kind == MNMT_EPI_F32_RESID;
+  if (tiles(256, 128) >= kFill && (K >= 1024 || !(int8_out || resid)))
+    return launch_cfg<256, 128, 2, 2, W4>(X, ldx, W, scale, bias, M, K, N, e, s);
+  // whole tiles with a residual over a long K: 8192 x 2048 x 512 23.7 against
+  // 28.5 us in 64 x 64 chunk tiles (cut off by M, 1500 x 2048 x 3000 is 32.6
+  // against 28.5 us: this kernel's checked stores read the residual word by word)
+  if (resid && K >= 1024 && M % 64 == 0 && N % 128 == 0 && tiles(128, 64) >= kFill)
+    return launch_cfg<128, 64, 2, 2, W4>(X, ldx, W, scale, bias, M, K, N, e, s);
+  // few tiles, one chunk of up to 128 bytes (4000 x 64 x 8000 12.4 against
+  // 13.1 us), or residual rows, which only the small tile loads ahead
+  // (2300 x 512 x 2100 14.1 against 20.8 us): 64 x 64; 3000 x 512 x 5001 to
+  // int8 18.4 against 23.2 us the other way
+  if (tiles(128, 64) < kFill || K <= 128 || resid) return launch_chunk<W4>(X, ldx, W, scale, bias, M, K, N, e, s);
+  return launch_chunk_kc<128, 128, W4>(X, ldx, W, scale, bias, M, K, N, e, s, 1);
 }
 
 }  // namespace
 
-// The weight-stationary kernel for K = 256 and long row runs (int8 weights);
-// the persistent kernel for whole tiles (16-byte aligned rows), K a
-// power-of-two number of chunks and enough tiles for every block; otherwise
-// the largest slab-pipelined tile that still gives about two blocks per CU
-// (256 CUs).
 hipError_t launch_gemm_split(const int8_t* X, int ldx, const int8_t* W, int M, int K, int N, int splits,
                              int32_t* part, hipStream_t s, bool w4) {
   if (M <= 0) return hipSuccess;
   if (splits < 1 || K % (splits * kBK)) return hipErrorInvalidValue;
   const EpiArgs e{MNMT_EPI_I32, part, N, 1.f, nullptr};
-  return w4 ? launch_cfg<64, 64, 2, 2, true>(X, ldx, W, nullptr, nullptr, M, K, N, e, s, splits)
-            : launch_cfg<64, 64, 2, 2, false>(X, ldx, W, nullptr, nullptr, M, K, N, e, s, splits);
+  return w4 ? launch_chunk<true>(X, ldx, W, nullptr, nullptr, M, K, N, e, s, splits)
+            : launch_chunk<false>(X, ldx, W, nullptr, nullptr, M, K, N, e, s, splits);
 }
 
+// The weight-stationary kernel for K = 256 and long row runs (int8 weights);
+// the persistent kernel for whole tiles (16-byte aligned rows), K a
+// power-of-two number of chunks and enough tiles for every block; otherwise
+// one tile per block (launch_tiled).
 hipError_t launch_gemm(const int8_t* X, int ldx, const int8_t* W, const float* scale, const float* bias, int M, int K,
                        int N, const EpiArgs& e, hipStream_t s, bool w4) {
   if (M <= 0) return hipSuccess;

@@ -181,6 +181,55 @@ def test_qlinear_wide_logits(torch_dev, M, K, N):
     assert (guard[M * N:] == -7.0).all(), "stores past the output"
 
 
+@pytest.mark.parametrize("M,K,N,bits", [
+    (65, 64, 1027, 8), (200, 256, 1090, 4), (129, 320, 1500, 8), (131, 512, 1093, 8), (100, 576, 1300, 4),
+    (600, 1088, 517, 8),  # 64 x 64 tiles: one to three chunks of K, the last one partly filled
+    (1501, 192, 2911, 8), (2111, 448, 2083, 4),  # 128 x 128 tiles
+    (1985, 1024, 8197, 8), (2048, 256, 8193, 8),  # 256 x 128 slab tiles (the second: the wide outputs)
+    (4096, 1024, 1024, 8),  # 128 x 64 slab tiles (the residual)
+], ids=lambda v: str(v))
+def test_qlinear_tiles_unaligned(torch_dev, M, K, N, bits):
+    """Tiles cut off by M and N, chunks of K that are not full, rows of no
+    16-byte multiple at an odd address, every epilogue, against the oracle;
+    nothing is stored outside the output."""
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+    from synth.modelfile import pack_int4
+
+    print(f"qlinear unaligned M={M} K={K} N={N} bits={bits}", flush=True)
+    rng = np.random.Generator(np.random.PCG64(M + K + N))
+    top = 127 if bits == 8 else 7
+    X = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
+    W = rng.integers(-top, top + 1, size=(N, K)).astype(np.int8)
+    scale = (rng.uniform(0.2, 1.0, size=N) / (40.0 * top * np.sqrt(K))).astype(np.float32)
+    bias = rng.normal(0.0, 20.0, size=N).astype(np.float32)
+    resid = rng.normal(0.0, 1.0, size=(M, N)).astype(np.float32)
+    packed = np.frombuffer(pack_int4(W), np.uint8).reshape(N, K // 2).copy() if bits == 4 else W
+    tW = _gpu(torch, dev, packed)
+    tX, ts, tb = (_gpu(torch, dev, a) for a in (X, scale, bias))
+    call = mnmt.mnmt_qlinear_w4 if bits == 4 else mnmt.mnmt_qlinear
+    rows = _rows_to_check(M, np.random.default_rng(N))
+    for epi, ref_epi, dt in ((mnmt.EPI_I32, None, torch.int32), (mnmt.EPI_I8, oracle.EPI_I8, torch.int8),
+                             (mnmt.EPI_I8_RELU, oracle.EPI_I8_RELU, torch.int8),
+                             (mnmt.EPI_F32, oracle.EPI_F32, torch.float32),
+                             (mnmt.EPI_F32_RESID, oracle.EPI_F32_RESID, torch.float32)):
+        guard = torch.full((M * N + 68,), 77, device=dev, dtype=dt)
+        out = guard[1:1 + M * N].view(M, N)
+        if epi == mnmt.EPI_F32_RESID:
+            out.copy_(torch.from_numpy(resid))
+        call(tX, tW, ts, tb, epi, 0.75, out=out)
+        torch.cuda.synchronize()
+        got = out[torch.from_numpy(rows).to(dev)].cpu().numpy()
+        if ref_epi is None:
+            ref = oracle.qgemm_i32(X[rows], W)
+        elif ref_epi == oracle.EPI_F32_RESID:
+            ref = oracle.qlinear(X[rows], W, scale, bias, ref_epi, gamma=0.75, resid=resid[rows])
+        else:
+            ref = oracle.qlinear(X[rows], W, scale, bias, ref_epi)
+        assert np.array_equal(got.view(np.uint8), np.ascontiguousarray(ref).view(np.uint8)), epi
+        assert guard[0] == 77 and (guard[1 + M * N:] == 77).all(), "stores outside the output"
+
+
 def test_binding_uses_the_current_stream(torch_dev):
     """Calls without a stream go to torch's current one, whichever that is at
     the time of the call."""
