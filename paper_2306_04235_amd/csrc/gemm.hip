@@ -4,9 +4,11 @@
 // GEMM; the epilogues of Section 4.2 applied as the tile is written).
 //
 // Tiles.  A 256-thread block owns a BN x BM tile of (output column n, row m);
-// its 4 waves split it WN x WM.  K is walked in 64-byte slabs staged through
-// LDS with double buffering: the next slab's global loads are in flight while
-// the current one feeds v_mfma_i32_32x32x32_i8, one LDS barrier per slab.
+// its 4 waves split it WN x WM.  K is walked in chunks of up to 512 bytes, one
+// memory round trip each (k_gemm_chunk), or, for a long K over large tiles, in
+// 64-byte slabs staged through LDS with double buffering (k_gemm: the next
+// slab's global loads are in flight while the current one feeds
+// v_mfma_i32_32x32x32_i8, one LDS barrier per slab).
 // Loads clamp their row index instead of branching, so rows past M or N read
 // valid memory and produce outputs that are never stored.
 //

@@ -9,9 +9,9 @@
 //    instruction reads 64 * 16 = 1024 contiguous bytes; U independent row
 //    groups per wave keep several loads in flight.  Products use the 4-way
 //    int8 dot instruction; the LPR partial sums meet in an xor butterfly.
-//  * qgemm_small: 8 < M <= 64 and K <= 1024 (the batch-1 encoder), and the
-//    batched decoder's 65-512-row projections of moderate N, 16x16x64
-//    matrix-core fragments loaded straight from memory.
+//  * qgemm_small: few rows or tiles and K <= 1024 (small_wins; and the
+//    layers with a row prologue), 16x16x64 matrix-core fragments loaded
+//    straight from memory.
 // Larger M runs the tiled matrix-core GEMM of gemm.hip.
 // Integer accumulation is exact, so neither kernel's order matters; the fp32
 // epilogue is the same single expression in both.
@@ -272,12 +272,10 @@ __global__ __launch_bounds__(64 * WAVES) void k_qgemm_small(FusedIn in, const in
 
 bool qgemm_small_fits(int M, int K) { return M >= 1 && M <= 64 && K <= kSmallMaxK && K % 64 == 0; }
 
-// Up to 256 rows and N <= 1024, or 512 rows and N <= 512, the one-round-trip
-// kernel (every block loads its weight fragments for all of K at once) also
-// beats the LDS-slab GEMM, whose 64x64 tiles leave such shapes with a few
-// dozen blocks (the batched decoder's projections and feed-forward layers).
-// At 512 rows with N >= 1536, or N = 2048, the repeated weight loads make it
-// the slower of the two.
+// Up to 256 rows and N <= 1024, or 512 rows and N <= 512, a layer of the
+// batched decoder normalizes its rows in this kernel's prologue (every block
+// loads its weight fragments for all of K at once).  At 512 rows with N >=
+// 1536, or N = 2048, the repeated weight loads make that the slower way.
 constexpr int kSmallMaxRows = 512;
 bool qgemm_rows_fit(int M, int K, int N) {
   return M >= 1 && (M <= 256 ? N <= 1024 : M <= kSmallMaxRows && N <= 512) && K <= kSmallMaxK && K % 64 == 0;
@@ -349,6 +347,25 @@ hipError_t launch_qgemm_split(const int8_t* X, int ldx, const int8_t* W, int M, 
   return launch_gemm_split(X, ldx, W, M, K, N, splits, part, s, w4);
 }
 
+// Where the fragment kernel is the faster one for a plain linear layer.  It
+// loads its operands row by row, 64 bytes of 16 rows at a time, and again in
+// every tile, so the 64 x 64 chunk tiles of gemm.hip pass it as the tiles and K
+// grow: at 64 rows from K = 256 on (64 x 256 x 768 3.2 against 2.8 us, 64 x 512
+// x 30001 18.5 against 4.9; below 64 rows a chunk tile's lower half is stored
+// element by element: 61 x 320 x 5222 3.7 against 4.0 us, 24 x 192 x 19042 3.7
+// against 4.3), in 16 x 16 blocks with their number (128 x 1024 x 1024, 512
+// blocks, 4.2 against 4.6 us; 256 x 256 x 768, 768 blocks, 3.1 against 2.8),
+// from 257 rows with the width (512 x 256 x 256 3.2 against 3.4 us, 512 x 512 x
+// 512 4.2 against 3.4).
+bool small_wins(int M, int K, int N) {
+  if (K > kSmallMaxK || K % 64) return false;
+  if (M < 64 || (K < 256 && qgemm_small_fits(M, K))) return true;
+  if (M == 64) return false;
+  if (!qgemm_rows_fit(M, K, N)) return false;
+  if (K < 256) return true;
+  return M <= 256 ? (M + 15) / 16 * ((N + 15) / 16) <= 640 : N <= 256;
+}
+
 hipError_t launch_qlinear(const int8_t* X, int ldx, const int8_t* W, const float* scale, const float* bias, int M,
                           int K, int N, const EpiArgs& e, hipStream_t s, bool w4) {
   if (M <= 0) return hipSuccess;
@@ -359,7 +376,7 @@ hipError_t launch_qlinear(const int8_t* X, int ldx, const int8_t* W, const float
     return w4 ? gemv_rows<true>(X, ldx, W, scale, bias, M, K, N, e, s)
               : gemv_rows<false>(X, ldx, W, scale, bias, M, K, N, e, s);
   if (e.kind == EPI_LOGITS_ARGMAX) return hipErrorInvalidValue;  // arg-max fusion is a batch-1 path
-  if (qgemm_small_fits(M, K) || qgemm_rows_fit(M, K, N))
+  if (small_wins(M, K, N))
     return launch_qgemm_small(nullptr, X, ldx, W, scale, bias, M, K, N, e, s, w4);
   return launch_gemm(X, ldx, W, scale, bias, M, K, N, e, s, w4);
 }

@@ -184,6 +184,7 @@ def test_qlinear_wide_logits(torch_dev, M, K, N):
 @pytest.mark.parametrize("M,K,N,bits", [
     (65, 64, 1027, 8), (200, 256, 1090, 4), (129, 320, 1500, 8), (131, 512, 1093, 8), (100, 576, 1300, 4),
     (600, 1088, 517, 8),  # 64 x 64 tiles: one to three chunks of K, the last one partly filled
+    (33, 128, 101, 8), (64, 1024, 1031, 4), (17, 64, 8209, 8), (250, 960, 777, 8), (300, 1024, 331, 4),  # up to 512 rows, both kernels
     (1501, 192, 2911, 8), (2111, 448, 2083, 4),  # 128 x 128 tiles
     (1985, 1024, 8197, 8), (2048, 256, 8193, 8),  # 256 x 128 slab tiles (the second: the wide outputs)
     (4096, 1024, 1024, 8),  # 128 x 64 slab tiles (the residual)
