@@ -187,7 +187,12 @@ void mnmt_model_free(mnmt_model* model);
 int mnmt_session_bytes(const mnmt_model* model, const mnmt_session_cfg* cfg, size_t* bytes);
 
 /* Create a session over a caller-allocated device workspace (>= the size
- * above, 256-byte aligned). */
+ * above, 256-byte aligned).  The call clears some words of the workspace and
+ * fills others (for batches, the layers' weights in the row-wise kernels'
+ * order) on a stream of its own, and returns when that is done.  It waits for
+ * no other stream, so every earlier use of the workspace's memory must have
+ * finished before the call: memory from an allocator that reuses blocks in
+ * stream order needs that stream synchronized first. */
 int mnmt_session_create(const mnmt_model* model, const mnmt_session_cfg* cfg, void* d_ws,
                         size_t ws_bytes, mnmt_session** out);
 void mnmt_session_free(mnmt_session* session);

@@ -302,6 +302,19 @@ class Model:
             self.close()
 
 
+def _settle(t):
+    """Wait for the work queued on the current stream of t's device.  The
+    allocator may hand out memory that queued kernels still use (it orders
+    reuse within that stream only), and mnmt_session_create fills the
+    workspace on a stream of its own."""
+    import torch
+
+    if t.is_cuda:
+        with torch.cuda.device(t.device):  # (memory of a capture is its graph's own)
+            if not torch.cuda.is_current_stream_capturing():
+                torch.cuda.current_stream(t.device).synchronize()
+
+
 class Session:
     """Decoding state of one model over a torch-allocated workspace."""
 
@@ -313,6 +326,7 @@ class Session:
         n = C.c_size_t()
         _check(lib().mnmt_session_bytes(model.handle, C.byref(self.cfg), C.byref(n)), "mnmt_session_bytes")
         self.ws = torch.empty(n.value, dtype=torch.uint8, device=model.arena.device)
+        _settle(self.ws)
         h = C.c_void_p()
         _check(lib().mnmt_session_create(model.handle, C.byref(self.cfg), _ptr(self.ws), self.ws.numel(),
                                          C.byref(h)), "mnmt_session_create")

@@ -164,3 +164,49 @@ def test_factorized_embedding_arena_and_validation():
         with pytest.raises(mnmt.MnmtError) as e:
             mnmt.mnmt_model_bytes(write_model(hdr, t2))
         assert e.value.status == mnmt.E_BAD_MODEL
+
+
+def test_session_waits_for_its_workspace(monkeypatch):
+    """A workspace from torch's allocator may still be in use by kernels
+    queued on the current stream, and mnmt_session_create fills it on a stream
+    of its own: the binding waits for that stream first (not under capture,
+    where waiting is not allowed and the memory is the graph's own)."""
+    import contextlib
+
+    import torch
+
+    calls = []
+
+    class Lib:
+        def __getattr__(self, name):
+            return lambda *a: calls.append(name) or 0
+
+    class Workspace:
+        is_cuda, device = True, "cuda:0"
+
+        def data_ptr(self):
+            return 256
+
+        def numel(self):
+            return 0
+
+    class Stream:
+        def synchronize(self):
+            calls.append("synchronize")
+
+    capturing = [False]
+    monkeypatch.setattr(mnmt, "lib", lambda: Lib())
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: Workspace())
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    monkeypatch.setattr(torch.cuda, "device", lambda d: contextlib.nullcontext())
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing[0])
+
+    class Model:
+        handle, arena = None, Workspace()
+
+    mnmt.Session(Model(), 1, 8, 8)
+    assert calls == ["mnmt_session_bytes", "synchronize", "mnmt_session_create"]
+    calls.clear()
+    capturing[0] = True
+    mnmt.Session(Model(), 1, 8, 8)
+    assert calls == ["mnmt_session_bytes", "mnmt_session_create"]

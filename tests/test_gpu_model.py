@@ -832,3 +832,35 @@ def test_session_capacity_errors(torch_dev):
         sess.decode_step()
     assert e.value.status == mnmt.E_CAPACITY
     sess.close()
+
+
+def test_session_over_memory_of_queued_work(torch_dev):
+    """A session whose workspace takes memory that kernels queued earlier still
+    write (freed and handed out again in stream order): it starts after them."""
+    import ctypes
+
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+
+    cfg = ROWS[2]
+    om, gm = _pair(cfg)
+    src, lens = G.make_sources(cfg.vocab, 5, [67, 64, 65, 1, 30], seed=311, s_max=67)
+    ts, tl = _t(torch, dev, src), _t(torch, dev, lens)
+    o_out, o_len = om.greedy(src, lens, 6)[:2]
+    n = ctypes.c_size_t()
+    sc = mnmt.SessionCfg(5, 67, 6, 1)
+    assert mnmt.lib().mnmt_session_bytes(gm.handle, ctypes.byref(sc), ctypes.byref(n)) == 0
+    old = torch.empty(n.value, dtype=torch.uint8, device=dev)
+    work = torch.empty(1 << 28, dtype=torch.uint8, device=dev)
+    torch.cuda.synchronize()
+    for k in range(50):
+        work.fill_(k)
+    old.fill_(0x5A)
+    at = old.data_ptr()
+    del old
+    sess = mnmt.Session(gm, 5, 67, 6, 1)
+    assert sess.ws.data_ptr() == at  # (the allocator's choice for an equal size)
+    out, out_len, _ = sess.translate(ts, tl, max_steps=6)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), o_out) and np.array_equal(out_len.cpu().numpy(), o_len)
+    sess.close()
