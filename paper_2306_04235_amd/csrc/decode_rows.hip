@@ -235,7 +235,7 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
   constexpr int QS = 3 * D + 16, HS = S::F + 16;  // row strides of act: q|k|v, hidden rows
   int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row0 = blockIdx.x * g.RB, rows = min(g.RB, g.R - row0);
-  const int dh = g.dh, h = g.h, T = g.T, t = g.t, nc = dh / 16, units = rows * h;
+  const int dh = g.dh, h = g.h, T = g.T, nc = dh / 16, units = rows * h;
   const int hs_s = (T + 63) / 64 * 64;
   // the wave's first (row, head) unit of the attention phases, and the steps
   // to its next ones (units wave, wave + WAVES, ...); the sentence's first row
@@ -250,6 +250,7 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
   Ring<S, W4> ring;
 #pragma unroll
   for (int b = 0; b < S::kRing; ++b) issue(ring, b, blob_rsrc<S, W4>(base), blob_rsrc<S, W4>(base), wave, lane);
+  const int t = g.t >= 0 ? g.t : min(max(*g.step, 0), T - 1);
 
   // A layer's LayerNorm constants (gain and bias of its three LayerNorms, 6 d
   // floats next to each other in the blob) pass through registers into LDS,
@@ -436,7 +437,7 @@ int waves_of(int d) { return d == 64 ? 4 : d == 128 ? 8 : d == 384 ? 12 : 16; }
 // The launch's LDS layout for RB rows per block.
 RowsLds rows_lds(const RowsArgs& g, int RB) {
   RowsLds l{};
-  const int keys = g.t + 1 > g.S ? g.t + 1 : g.S, w = waves_of(g.d);
+  const int own = g.t < 0 ? g.T : g.t + 1, keys = own > g.S ? own : g.S, w = waves_of(g.d);
   l.np = (keys + 63) / 64 * 64;
   l.ln = align16(RB * (g.d + 4) * 4);
   l.a = l.ln + 24 * g.d;
@@ -563,8 +564,8 @@ int rows_per_block(const RowsArgs& g) {
 }  // namespace
 
 hipError_t launch_dec_rows(const RowsArgs& args, hipStream_t s) {
-  if ((size_t)args.R * args.T * args.d >> 31) return hipErrorInvalidValue;  // KvAt's offsets
-  if (args.R < 1 || args.t < 0 || args.t >= args.T || !dec_rows_shape(args.d, args.dh, args.F))
+  if ((size_t)args.R * args.T * args.d >> 31) return hipErrorInvalidValue;  // load_chunks' offsets
+  if (args.R < 1 || args.t >= args.T || (args.t < 0 && !args.step) || !dec_rows_shape(args.d, args.dh, args.F))
     return hipErrorInvalidValue;
   RowsParams P{args, {}};
   P.g.RB = rows_per_block(args);

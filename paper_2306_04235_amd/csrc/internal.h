@@ -641,7 +641,9 @@ struct RowsArgs {
   float* x;                 // [R, d] input rows (tok null); the final residual rows on return
   int8_t* out;              // [R, d] the output projection's int8 input
   int R, W, RB;             // rows, rows per sentence, rows per block (set by the launcher)
-  int d, dh, h, F, T, S, t;
+  int d, dh, h, F, T, S;
+  int t;                    // position of the step; < 0: *step (a step replayed from the caller's graph moves on)
+  const int* step;
   int8_t* kcache;           // layer l at + l * cache_stride: [R][T][d]
   int8_t* vcache;
   size_t cache_stride;

@@ -739,8 +739,9 @@ int run_decoder_layers(mnmt_session* S, int R, int W, bool beam, hipStream_t s, 
 // against 3.83 ms, 8 rows 3.71 against 4.14 ms).
 bool rows_used(const mnmt_session* S, int R) { return S->rows_blobs && (R > 3 || S->m->info.d_model < 512); }
 
-// One decoder step for R rows in one launch (decode_rows.hip): position t,
-// input tokens cur_tok; ends as run_decoder_layers does.
+// One decoder step for R rows in one launch (decode_rows.hip): position t
+// (< 0: the device step counter's), input tokens cur_tok; ends as
+// run_decoder_layers does.
 int run_decoder_rows(mnmt_session* S, int R, int W, bool beam, int t, hipStream_t s) {
   const mnmt_model* m = S->m;
   if (factored(m)) {
@@ -772,6 +773,7 @@ int run_decoder_rows(mnmt_session* S, int R, int W, bool beam, int t, hipStream_
   a.T = S->cfg.max_tgt_len;
   a.S = S->S;
   a.t = t;
+  a.step = S->step;
   a.kcache = S->kcache[0];
   a.vcache = S->vcache[0];
   a.cross = S->cross_kv[0];
@@ -786,7 +788,8 @@ int run_decoder_rows(mnmt_session* S, int R, int W, bool beam, int t, hipStream_
 }
 
 // Greedy step: layers, tied output projection with fused arg-max (batch <= 8,
-// operator by operator) or logits + row arg-max, then bookkeeping.  logits_out: optional [R, V].
+// operator by operator) or logits + row arg-max, then bookkeeping.
+// t: run_decoder_rows'.  logits_out: optional [R, V].
 int greedy_step(mnmt_session* S, int R, int t, int stop_at_eos, float* logits_out, hipStream_t s) {
   const mnmt_model* m = S->m;
   int rc = rows_used(S, R) ? run_decoder_rows(S, R, 1, false, t, s) : run_decoder_layers(S, R, 1, false, s);
@@ -1249,11 +1252,14 @@ int embed_step_input(mnmt_session* S, int R, hipStream_t s) {
 
 // The greedy step for R rows on the fastest path that fits.
 // On the 1-2 row path the input rows must be in dec_x (embed_step_input).
+// A step of a whole translation (fold) is enqueued for its position t alone;
+// a single one may be replayed, so where a path can it takes the position from
+// the device step counter.
 int greedy_step_any(mnmt_session* S, int R, int t, int stop_at_eos, float* logits_out, hipStream_t s,
                     bool fold = false, bool last = false, Chain* ch = nullptr) {
   if (step_path_used(S, R)) return greedy_step_v3(S, R, t, stop_at_eos, logits_out, s, fold, last, ch);
   if (R <= 8 && !factored(S->m) && !rows_used(S, R)) return greedy_step_fused(S, R, t, stop_at_eos, logits_out, s);
-  return greedy_step(S, R, t, stop_at_eos, logits_out, s);
+  return greedy_step(S, R, fold ? t : -1, stop_at_eos, logits_out, s);
 }
 
 // Step t of `steps`: from the second step on, the input rows come from the

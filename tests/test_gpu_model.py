@@ -864,3 +864,39 @@ def test_session_over_memory_of_queued_work(torch_dev):
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), o_out) and np.array_equal(out_len.cpu().numpy(), o_len)
     sess.close()
+
+
+OPER = G.ModelConfig("oper-256", 256, 4, 768, 2, 2, 300, ln_post=0, seed=321, random_gamma=True, weight_std=0.1)
+
+
+@pytest.mark.parametrize("cfg,B", [(ROWS[2], 12), (ROWS[5], 5), (ROWS[8], 5), (FACTOR, 12), (OPER, 12)],
+                         ids=lambda v: getattr(v, "name", str(v)))
+def test_replayed_decode_step(torch_dev, cfg, B):
+    """One decode step captured in the caller's graph decodes the next position
+    at each replay (the step index lives in device memory): logits of every
+    step against the oracle, with eager work of the caller between replays."""
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+
+    om, gm = _pair(cfg)
+    steps = 7
+    src, lens = G.make_sources(cfg.vocab, B, (2, 20), seed=322, s_max=20)
+    o_out, _, o_logits = om.greedy(src, lens, steps, want_logits=True)
+    sess = mnmt.Session(gm, B, 20, steps, 1)
+    ts, tl = _t(torch, dev, src), _t(torch, dev, lens)
+    sess.encode(ts, tl)
+    sess.decode_step()  # (the first call outside a capture)
+    sess.encode(ts, tl)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        nxt, logits = sess.decode_step(want_logits=True)
+    other = torch.ones(1000, device=dev)
+    for t in range(steps):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(nxt.cpu().numpy(), o_out[:, t]), f"tokens of step {t}"
+        ref = np.ascontiguousarray(o_logits[:, t])
+        assert np.array_equal(logits.cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"logits of step {t}"
+        other.mul_(1.01)
+    sess.close()
