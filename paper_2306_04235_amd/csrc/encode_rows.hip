@@ -61,7 +61,8 @@ __global__ __launch_bounds__((64 * EncShape<KQ, FQ>::WAVES)) void k_enc_rows(Enc
   const int row0 = blockIdx.x * RB, rows = min(RB, g.R - row0);
   // nothing to do for rows past their sentence's end (they are never read)
   bool live = false;
-  for (int b = row0 / g.S; b * g.S < row0 + rows; ++b) live = live || max(row0, b * g.S) < b * g.S + g.len[b];
+  for (int b = row0 / g.S; b * g.S < row0 + rows; ++b)  // (lengths clamped to 1..S, as the attention reads them)
+    live = live || max(row0, b * g.S) < b * g.S + min(max(g.len[b], 1), g.S);
   if (!live) return;
 
   const Blob bl = blob_rsrc<S, W4>(g.blob);

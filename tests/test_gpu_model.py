@@ -900,3 +900,35 @@ def test_replayed_decode_step(torch_dev, cfg, B):
         assert np.array_equal(logits.cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"logits of step {t}"
         other.mul_(1.01)
     sess.close()
+
+
+@pytest.mark.parametrize("B", [2, 70])
+def test_lengths_outside_the_range_are_clamped(torch_dev, B):
+    """Source lengths below 1 read as 1 and above S as S, in the small and the
+    row-wise encoder: the same bytes as with the clamped lengths (the buffers
+    hold another batch's rows before, so that a row left out shows)."""
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+
+    cfg = ROWS[2]
+    _, gm = _pair(cfg)
+    S, d = 16, cfg.d_model
+    rng = np.random.Generator(np.random.PCG64(323))
+    lens = rng.integers(1, S + 1, B).astype(np.int32)
+    lens[:2] = [0, S + 9]
+    if B > 8:
+        lens[4:8] = [-5, -2**31, 2**31 - 1, 0]
+    ok = np.clip(lens, 1, S).astype(np.int32)
+    src, _ = G.make_sources(cfg.vocab, B, [S] * B, seed=324, s_max=S)
+    other, _ = G.make_sources(cfg.vocab, B, [S] * B, seed=325, s_max=S)
+    out = []
+    for n in (ok, lens):
+        sess = mnmt.Session(gm, B, S, 2, 1)
+        sess.encode(_t(torch, dev, other), _t(torch, dev, np.full(B, S, np.int32)))
+        sess.encode(_t(torch, dev, src), _t(torch, dev, n))
+        nxt, z = sess.decode_step(want_logits=True)
+        enc = sess.tensor("cross_kv.0", torch.int8, (B, S, 2 * d)).cpu().numpy()
+        out.append((np.concatenate([enc[b, : ok[b]] for b in range(B)]), nxt.cpu().numpy(), z.cpu().numpy()))
+        sess.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
