@@ -25,6 +25,8 @@
 // Placement.  Blocks are dispatched to the 8 XCDs round-robin; the linear
 // block id is remapped so that each XCD works through one contiguous range of
 // tiles (m fastest), which keeps the W and X tiles it shares in its own L2.
+#include <algorithm>
+
 #include "blocks.hpp"
 #include "internal.h"
 
@@ -932,6 +934,23 @@ hipError_t launch_gemm(const int8_t* X, int ldx, const int8_t* W, const float* s
                        int N, const EpiArgs& e, hipStream_t s, bool w4) {
   if (M <= 0) return hipSuccess;
   if (K % kBK) return hipErrorInvalidValue;
+  // the tiles' loads have 32-bit offsets: operands past 4 GiB in ranges of
+  // columns and rows (whole tiles of either kernel)
+  const size_t wrow = w4 ? K / 2 : K, most = (1ull << 32) - 1;
+  if ((size_t)N * wrow > most || (size_t)M * ldx > most) {
+    const long cols = most / wrow / 256 * 256, rows = most / ldx / 256 * 256;
+    const int out_bytes = e.kind == MNMT_EPI_I8 || e.kind == MNMT_EPI_I8_RELU ? 1 : 4;
+    for (long n = 0; n < N; n += cols)
+      for (long m = 0; m < M; m += rows) {
+        EpiArgs part = e;
+        part.out = static_cast<int8_t*>(e.out) + ((size_t)m * e.ldo + n) * out_bytes;
+        const hipError_t r = launch_gemm(X + (size_t)m * ldx, ldx, W + (size_t)n * wrow, scale ? scale + n : nullptr,
+                                         bias ? bias + n : nullptr, (int)std::min(rows, M - m), K,
+                                         (int)std::min(cols, N - n), part, s, w4);
+        if (r != hipSuccess) return r;
+      }
+    return hipSuccess;
+  }
   const bool int8_out = e.kind == MNMT_EPI_I8 || e.kind == MNMT_EPI_I8_RELU;
   const bool aligned = (reinterpret_cast<uintptr_t>(e.out) & 15) == 0 && e.ldo % (int8_out ? 16 : 4) == 0;
   const bool ops_aligned = ldx % 16 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0 &&

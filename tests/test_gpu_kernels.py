@@ -231,6 +231,29 @@ def test_qlinear_tiles_unaligned(torch_dev, M, K, N, bits):
         assert guard[0] == 77 and (guard[1 + M * N:] == 77).all(), "stores outside the output"
 
 
+@pytest.mark.parametrize("M,K,N", [(64, 1024, 4194304 + 513), (64, 512, 8388608 + 513)])
+def test_qlinear_weights_past_4_gib(torch_dev, M, K, N):
+    """Weights of more than 2^32 bytes, in ranges of columns (the slab and the
+    chunk tiles of 64 rows): sampled columns on both sides of the 4 GiB line."""
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+
+    print(f"qlinear past 4 GiB M={M} K={K} N={N}", flush=True)
+    g = torch.Generator(device=dev).manual_seed(N)
+    X = torch.randint(-127, 128, (M, K), generator=g, device=dev, dtype=torch.int8)
+    W = torch.randint(-127, 128, (N, K), generator=g, device=dev, dtype=torch.int8)
+    scale = torch.rand(N, generator=g, device=dev) * (40.0 / (74 * 74 * K ** 0.5))
+    bias = torch.randn(N, generator=g, device=dev)
+    out = mnmt.mnmt_qlinear(X, W, scale, bias, mnmt.EPI_I8)
+    line = (1 << 32) // K
+    cols = np.unique(np.concatenate([np.arange(70), np.arange(line - 130, line + 400), np.arange(N - 70, N),
+                                     np.random.default_rng(5).integers(0, N, 200)]))
+    at = torch.from_numpy(cols).to(dev)
+    ref = oracle.qlinear(X.cpu().numpy(), W[at].cpu().numpy(), scale[at].cpu().numpy(), bias[at].cpu().numpy(),
+                         oracle.EPI_I8)
+    assert np.array_equal(out[:, at].cpu().numpy(), ref)
+
+
 def test_binding_uses_the_current_stream(torch_dev):
     """Calls without a stream go to torch's current one, whichever that is at
     the time of the call."""
