@@ -795,6 +795,7 @@ struct mnmt_session {
   int32_t* rows_index = nullptr;     // blob number of each layer (null: its own)
   bool rows_w4 = false;              // their weights are packed 4-bit codes
   int8_t* enc_blobs = nullptr;       // the row-wise encoder's passes (null: not used)
+  std::vector<int32_t> enc_number;   // blob number of each pass
   bool enc_w4 = false;
   int32_t* cur_tok = nullptr;
   int* step = nullptr;

@@ -7,6 +7,7 @@
 // decoder's fp32 logits, which are only needed after encoding has finished.
 // Each layer reuses the same few buffers: one fp32 residual stream and int8
 // buffers for the sublayer input, attention context and FFN hidden layer.
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -54,16 +55,40 @@ bool rows_w4(const mnmt_model* m) {
   return true;
 }
 
-// Number of each decoder layer's blob: layers that share parameters share it,
-// except that in post-LN models the LayerNorm in front of a layer is the
-// previous layer's, so there each layer has its own.
+// Number of each row-wise pass's blob, whose contents follow from the
+// parameters of two neighbouring layers (pass p: layers p - 1 and p; alias:
+// the layer whose parameters a layer shares, or -1): equal pairs share a blob.
+// Layers -1 and n, past the ends, are their own.
+std::vector<int32_t> pass_numbers(const std::vector<int>& alias, size_t passes) {
+  auto root = [&](int l) {
+    while (l >= 0 && l < (int)alias.size() && alias[l] >= 0) l = alias[l];
+    return l;
+  };
+  std::vector<std::pair<int, int>> seen;
+  std::vector<int32_t> num;
+  for (int p = 0; p < (int)passes; ++p) {
+    const std::pair<int, int> key{root(p - 1), root(p)};
+    size_t i = 0;
+    while (i < seen.size() && seen[i] != key) ++i;
+    if (i == seen.size()) seen.push_back(key);
+    num.push_back((int32_t)i);
+  }
+  return num;
+}
+size_t blob_count(const std::vector<int32_t>& num) { return (size_t)*std::max_element(num.begin(), num.end()) + 1; }
+
+// A decoder layer's blob: its own parameters, and in post-LN models the
+// previous layer's last LayerNorm, which its Q/K/V projection follows.
 std::vector<int32_t> rows_numbers(const mnmt_model* m) {
+  if (m->info.ln_post) return pass_numbers(m->dec_alias, m->dec.size());
   std::vector<int32_t> n(m->dec.size());
   int32_t next = 0;
-  for (size_t l = 0; l < n.size(); ++l)
-    n[l] = m->dec_alias[l] >= 0 && !m->info.ln_post ? n[m->dec_alias[l]] : next++;
+  for (size_t l = 0; l < n.size(); ++l) n[l] = m->dec_alias[l] >= 0 ? n[m->dec_alias[l]] : next++;
   return n;
 }
+
+// An encoder pass's: from layer p - 1's attention to layer p's Q/K/V.
+std::vector<int32_t> enc_numbers(const mnmt_model* m) { return pass_numbers(m->enc_alias, m->enc.size() + 1); }
 
 // Bytes of the row-wise decoder's blobs, or 0 for a session that does not
 // use them: models of other shapes, sessions of at most 2 rows (their step
@@ -73,9 +98,7 @@ size_t rows_blobs_bytes(const mnmt_model* m, const mnmt_session_cfg& c) {
   const size_t R = (size_t)c.max_batch * c.beam;
   if (R < 3 || R * c.max_tgt_len * m->info.d_model >> 31 || !dec_rows_shape(m->info.d_model, m->dh, m->info.d_ffn))
     return 0;
-  size_t n = 0;
-  for (int32_t i : rows_numbers(m)) n = (size_t)i + 1 > n ? i + 1 : n;
-  return n * dec_rows_blob_bytes(m->info.d_model, m->info.d_ffn, rows_w4(m));
+  return blob_count(rows_numbers(m)) * dec_rows_blob_bytes(m->info.d_model, m->info.d_ffn, rows_w4(m));
 }
 
 // The row-wise encoder: packed 4-bit rows when every layer has them; blobs
@@ -89,7 +112,7 @@ bool enc_rows_w4(const mnmt_model* m) {
 size_t enc_blobs_bytes(const mnmt_model* m, const mnmt_session_cfg& c) {
   if ((size_t)c.max_batch * c.max_src_len <= kEncAccRows || !dec_rows_shape(m->info.d_model, m->dh, m->info.d_ffn))
     return 0;
-  return (m->enc.size() + 1) * enc_rows_blob_bytes(m->info.d_model, m->info.d_ffn, enc_rows_w4(m));
+  return blob_count(enc_numbers(m)) * enc_rows_blob_bytes(m->info.d_model, m->info.d_ffn, enc_rows_w4(m));
 }
 
 int validate_cfg(const mnmt_model* m, const mnmt_session_cfg* c) {
@@ -496,7 +519,7 @@ int run_encoder_rows(mnmt_session* S, hipStream_t s) {
   g.dh = m->dh;
   g.F = F;
   for (size_t l = 0; l <= m->enc.size(); ++l) {  // pass l follows layer l - 1's attention
-    g.blob = S->enc_blobs + l * bytes;
+    g.blob = S->enc_blobs + S->enc_number[l] * bytes;
     g.first = l == 0;
     g.last = l == m->enc.size();
     g.out = g.last ? S->enc_out : S->enc_qkv;
@@ -508,20 +531,23 @@ int run_encoder_rows(mnmt_session* S, hipStream_t s) {
   return MNMT_OK;
 }
 
-// Write the row-wise encoder's blobs.
-hipError_t pack_encoder(const mnmt_model* m, int8_t* blobs, bool w4, hipStream_t s) {
+// Write the row-wise encoder's blobs (each number's first pass).
+hipError_t pack_encoder(const mnmt_model* m, const std::vector<int32_t>& num, int8_t* blobs, bool w4, hipStream_t s) {
   const int d = m->info.d_model, F = m->info.d_ffn;
   const bool post = m->info.ln_post;
   const size_t bytes = enc_rows_blob_bytes(d, F, w4), n = m->enc.size();
   hipError_t e = hipSuccess;
+  int32_t done = 0;
   for (size_t l = 0; l <= n && e == hipSuccess; ++l) {
+    if (num[l] < done) continue;
     const LayerDev* L = l ? &m->enc[l - 1] : nullptr;
     const LayerDev* N = l < n ? &m->enc[l] : nullptr;
     // post-LN: the layer's own LayerNorms follow its sublayers
     const LnDev& ff = L ? (post ? L->sa_ln : L->ff_ln) : m->enc[0].ff_ln;
     const LnDev& nx = post ? (L ? L->ff_ln : m->enc[0].sa_ln) : (N ? N->sa_ln : m->enc_ln);
     e = launch_enc_rows_pack(L, N ? &N->qkv : nullptr, ff, nx, N ? N->qkv.inv_in : m->inv_enc, d, F, w4,
-                             blobs + l * bytes, s);
+                             blobs + num[l] * bytes, s);
+    ++done;
   }
   return e;
 }
@@ -1530,7 +1556,8 @@ extern "C" int mnmt_session_create(const mnmt_model* model, const mnmt_session_c
   if (h == hipSuccess && p.enc_blobs_bytes) {
     S->enc_blobs = (int8_t*)at(p.enc_blobs);
     S->enc_w4 = enc_rows_w4(model);
-    h = pack_encoder(model, S->enc_blobs, S->enc_w4, S->capture_stream);
+    S->enc_number = enc_numbers(model);
+    h = pack_encoder(model, S->enc_number, S->enc_blobs, S->enc_w4, S->capture_stream);
   }
   if (h == hipSuccess) h = hipStreamSynchronize(S->capture_stream);
   if (h != hipSuccess) {

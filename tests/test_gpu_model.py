@@ -932,3 +932,41 @@ def test_lengths_outside_the_range_are_clamped(torch_dev, B):
         sess.close()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+def test_sessions_share_copies_of_shared_layers(torch_dev):
+    """A batch session's copies of the layers' weights: layers that share
+    parameters share them, in the encoder too (pre- and post-LN), and the
+    results are those of the same model with every layer written out."""
+    import ctypes
+
+    from tests.test_oracle_model import _unshare
+
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+
+    base = dataclasses.replace(SHARED_256, vocab=500, n_enc=6, n_dec=3)
+    for post in (0, 1):
+        blob = G.build_model(dataclasses.replace(base, name=f"shared-copies-{post}", ln_post=post))
+        models = [mnmt.Model(blob), mnmt.Model(_unshare(blob))]
+        src, lens = G.make_sources(500, 5, (3, 30), seed=326, s_max=30)
+        sizes, outs = [], []
+        for m in models:
+            n = ctypes.c_size_t()
+            sc = mnmt.SessionCfg(5, 30, 8, 1)
+            assert mnmt.lib().mnmt_session_bytes(m.handle, ctypes.byref(sc), ctypes.byref(n)) == 0
+            sizes.append(n.value)
+            sess = mnmt.Session(m, 5, 30, 8, 1)
+            out = sess.translate(_t(torch, dev, src), _t(torch, dev, lens), max_steps=8)
+            keys = sess.tensor("out_key", torch.int64, (8, 5))
+            torch.cuda.synchronize()
+            outs.append((out[0].cpu().numpy(), keys.cpu().numpy()))
+            sess.close()
+        d, F = base.d_model, base.d_ffn
+        enc, dec = 4 * d * d + 2 * d * F, 6 * d * d + 2 * d * F  # weights of a pass and of a decoder layer
+        # 7 encoder passes against 4 (two ends, (0, 1), (1, 0)); 3 decoder layers against 2 (post-LN: 3)
+        saved = 3 * enc + (0 if post else dec)
+        assert saved <= sizes[1] - sizes[0] < saved + 4 * 65536
+        assert all(np.array_equal(a, b) for a, b in zip(*outs))
+        for m in models:
+            m.close()
