@@ -47,19 +47,10 @@
 #include "blocks.hpp"
 #include "internal.h"
 #include "rows.hpp"
+#include "rows_plan.hpp"
 
 namespace mnmt {
 namespace {
-
-constexpr int kVtStride = 17;           // dwords per column of the transposed values (odd: no bank conflicts)
-constexpr int kVtBytes = 64 * kVtStride * 4;
-
-// LDS layout, sized by the host for the launch (byte offsets, 16-aligned).
-struct RowsLds {
-  int ln, a, hist, act, p, total;  // LayerNorm constants, int8 input rows, cache-row history, q|k|v rows, the waves'
-                                   // attention scratch; the hidden rows lie over the last two
-  int np;                          // softmax weights per wave
-};
 
 struct RowsParams {
   RowsArgs g;
@@ -81,7 +72,7 @@ struct RowsHdr {
 template <int KQ_, int FQ_>
 struct Shape {
   static constexpr int KQ = KQ_, FQ = FQ_, D = 64 * KQ, F = 64 * FQ;
-  static constexpr int WAVES = KQ == 1 ? 4 : KQ == 2 ? 8 : KQ == 6 ? 12 : 16;
+  static constexpr int WAVES = rows_waves(D);
   static constexpr int C = KQ <= 2 ? 1 : KQ == 6 ? 3 : 2;
   static constexpr int kRing = KQ == 1 ? 2 : 4;
   static constexpr int NCH = KQ / C, NCH2 = FQ / C;             // batches per tile: K = d, K = F
@@ -430,25 +421,6 @@ __global__ __launch_bounds__((64 * Shape<KQ, FQ>::WAVES)) void k_dec_rows(RowsPa
   }
 }
 
-int align16(int v) { return (v + 15) / 16 * 16; }
-
-int waves_of(int d) { return d == 64 ? 4 : d == 128 ? 8 : d == 384 ? 12 : 16; }
-
-// The launch's LDS layout for RB rows per block.
-RowsLds rows_lds(const RowsArgs& g, int RB) {
-  RowsLds l{};
-  const int own = g.t < 0 ? g.T : g.t + 1, keys = own > g.S ? own : g.S, w = waves_of(g.d);
-  l.np = (keys + 63) / 64 * 64;
-  l.ln = align16(RB * (g.d + 4) * 4);
-  l.a = l.ln + 24 * g.d;
-  l.hist = align16(l.a + RB * (g.d + 16));
-  l.act = align16(l.hist + RB * ((g.T + 63) / 64 * 64));
-  l.p = align16(l.act + RB * (3 * g.d + 16));
-  const int att = l.p + (RB * g.h < w ? RB * g.h : w) * (l.np * 4 + kVtBytes), hid = l.act + RB * (g.F + 16);
-  l.total = att > hid ? att : hid;
-  return l;
-}
-
 template <int KQ, int FQ>
 hipError_t launch_shape(const RowsParams& P, int blocks, hipStream_t s) {
   auto go = [&](auto kern) -> hipError_t {
@@ -547,31 +519,16 @@ hipError_t launch_dec_rows_pack(const LayerDev& L, const LnDev& ln_self, bool po
   return launch_rows_pack(p, lin, 6, O.c, O.n, O.w, w4, s);
 }
 
-namespace {
-
-// Rows per block: the grid reaches 256 blocks (one per CU) with as few rows
-// per block as possible, up to the 16 rows of a tile, the waves of a block
-// (one LayerNorm row each) and the LDS of a CU; past that, the fewest rounds
-// of 256 blocks, evenly filled (4096 rows of the base model: two rounds of 8
-// rows against a full and a nearly empty one of 11).
-int rows_per_block(const RowsArgs& g) {
-  int most = waves_of(g.d);
-  while (most > 1 && rows_lds(g, most).total > kRowsMaxLds) --most;
-  const int rounds = (g.R + 256 * most - 1) / (256 * most);
-  return (g.R + 256 * rounds - 1) / (256 * rounds);
-}
-
-}  // namespace
-
 hipError_t launch_dec_rows(const RowsArgs& args, hipStream_t s) {
   if ((size_t)args.R * args.T * args.d >> 31) return hipErrorInvalidValue;  // load_chunks' offsets
   if (args.R < 1 || args.t >= args.T || (args.t < 0 && !args.step) || !dec_rows_shape(args.d, args.dh, args.F))
     return hipErrorInvalidValue;
   RowsParams P{args, {}};
-  P.g.RB = rows_per_block(args);
-  P.l = rows_lds(args, P.g.RB);
+  const RowsPlan plan = rows_plan(RowsSizes{args.R, args.d, args.h, args.F, args.T, args.S, args.t});
+  P.g.RB = plan.rows;
+  P.l = plan.lds;
   if (P.l.total > kRowsMaxLds) return hipErrorInvalidValue;
-  const int blocks = (args.R + P.g.RB - 1) / P.g.RB;
+  const int blocks = plan.blocks;
   switch (args.d) {
     case 64: return launch_kq<1>(P, blocks, s);
     case 128: return launch_kq<2>(P, blocks, s);

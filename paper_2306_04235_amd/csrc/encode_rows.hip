@@ -13,6 +13,7 @@
 #include "blocks.hpp"
 #include "internal.h"
 #include "rows.hpp"
+#include "rows_plan.hpp"
 
 namespace mnmt {
 namespace {
@@ -21,7 +22,7 @@ namespace {
 template <int KQ_, int FQ_>
 struct EncShape {
   static constexpr int KQ = KQ_, FQ = FQ_, D = 64 * KQ, F = 64 * FQ;
-  static constexpr int WAVES = KQ == 1 ? 4 : KQ == 2 ? 8 : KQ == 6 ? 12 : 16;
+  static constexpr int WAVES = rows_waves(D);
   static constexpr int C = KQ <= 2 ? 1 : KQ == 6 ? 3 : 2;
   static constexpr int kRing = KQ == 1 ? 2 : 4;
   static constexpr int NCH = KQ / C, NCH2 = FQ / C;

@@ -652,7 +652,6 @@ struct RowsArgs {
   const int32_t* len;       // [B]
   const int32_t* hist;      // [2][R][T] position -> cache row (beam), or null
 };
-constexpr int kRowsMaxLds = 160 * 1024;
 bool dec_rows_shape(int d, int dh, int F);
 size_t dec_rows_blob_bytes(int d, int F, bool w4);
 hipError_t launch_dec_rows_pack(const LayerDev& L, const LnDev& ln_self, bool post, bool w4, int8_t* blob,

@@ -970,3 +970,45 @@ def test_sessions_share_copies_of_shared_layers(torch_dev):
         assert all(np.array_equal(a, b) for a, b in zip(*outs))
         for m in models:
             m.close()
+
+
+@pytest.mark.parametrize("cfg,B,steps", [
+    (ROWS[5], 4090, 3), (ROWS[4], 4090, 3), (ROWS[6], 3070, 3), (ROWS[9], 2050, 3), (ROWS[8], 1300, 3),
+    (ROWS[2], 2000, 3), (ROWS[0], 1020, 4),  # 16, 16, 12, 9, 6, 8 and 4 rows per block
+    (ROWS[9], 4090, 200),  # 16 rows per block, from 128 positions on 8 (LDS)
+], ids=lambda v: getattr(v, "name", str(v)))
+def test_row_wise_decoder_many_rows_per_block(torch_dev, cfg, B, steps):
+    """Greedy search with up to 16 rows per block and a last block that is not
+    full: a sample of sentences from all over the batch against the oracle,
+    and the logits of single steps (whose launches are laid out for the
+    longest target)."""
+    torch, dev = torch_dev
+    from paper_2306_04235_amd import mnmt
+
+    om, gm = _pair(cfg)
+    src, lens = G.make_sources(cfg.vocab, B, (1, 9), seed=327, s_max=9)
+    idx = np.unique(np.concatenate([[0, 15, 16, B // 2, B - 11, B - 1],
+                                    np.random.default_rng(B).integers(0, B, 24 if steps < 10 else 2)]))
+    print(f"greedy {cfg.name} B={B} steps={steps}", flush=True)
+    o_out, _, o_logits = om.greedy(src[idx], lens[idx], steps, want_logits=True)
+    sess = mnmt.Session(gm, B, 9, steps, 1)
+    ts, tl = _t(torch, dev, src), _t(torch, dev, lens)
+    at = torch.from_numpy(idx).to(dev)
+    out, _, _ = sess.translate(ts, tl, max_steps=steps)
+    assert np.array_equal(out[at].cpu().numpy(), o_out)
+    sess.encode(ts, tl)
+    for t in range(3):
+        nxt, z = sess.decode_step(want_logits=True)
+        assert np.array_equal(nxt[at].cpu().numpy(), o_out[:, t])
+        ref = np.ascontiguousarray(o_logits[:, t])
+        assert np.array_equal(z[at].cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"logits of step {t}"
+    sess.close()
+
+
+@pytest.mark.parametrize("i,B,W", [(5, 511, 8), (9, 300, 7)])
+def test_row_wise_decoder_many_rows_per_block_beam(torch_dev, i, B, W):
+    """Beam search with 16 and 9 rows per block, blocks that cross sentences."""
+    torch, dev = torch_dev
+    src, lens = G.make_sources(ROWS[i].vocab, B, (1, 9), seed=328, s_max=9)
+    idx = np.unique(np.concatenate([[0, 1, B // 2, B - 1], np.random.default_rng(B).integers(0, B, 12)]))
+    _beam_check(torch, dev, ROWS[i], src, lens, W, 5, 0.6, sample=idx)
