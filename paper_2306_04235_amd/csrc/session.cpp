@@ -759,11 +759,20 @@ int run_decoder_layers(mnmt_session* S, int R, int W, bool beam, hipStream_t s, 
   return ln_rows(post ? last.ff_ln : m->dec_ln, m->inv_fin, false);
 }
 
-// The row-wise decoder runs every step whose session holds its blobs, except
-// 3 rows at width 512: a block's stream of 3.7 MB per layer then takes longer
-// than the launches it replaces (12 steps: 3.55 against 2.91 ms; 4 rows 3.72
-// against 3.83 ms, 8 rows 3.71 against 4.14 ms).
-bool rows_used(const mnmt_session* S, int R) { return S->rows_blobs && (R > 3 || S->m->info.d_model < 512); }
+// Whether R rows' steps run in the row-wise decoder (where the session holds
+// its blobs).  A block streams every weight of a layer whatever the rows, while
+// the launches it replaces cost more with each row: 12 greedy steps of base (d
+// 512, F 2048) take 3.45 ms row-wise against 2.85, 3.15, 3.55 and 4.11 ms for
+// 3, 4, 5 and 8 rows (4-bit weights 3.25 against the same), with F 1024 2.69
+// against 2.54, 2.79 and 2.96 ms for 1, 3 and 4, d 384 with F 1536 1.24 against
+// 1.56 ms for 3, narrower models less from the first row on.  Beam search,
+// whose launches are dearer, gains one row earlier (base, 24 steps: 6.9 against
+// 6.6 and 7.1 ms for 3 and 4 rows).  So a row is worth half a million codes of
+// a layer past the first 1.5 million.
+bool rows_used(const mnmt_session* S, int R, bool beam) {
+  const long d = S->m->info.d_model, codes = 6 * d * d + 2 * d * S->m->info.d_ffn;
+  return S->rows_blobs && 500000L * (R + beam) >= codes - 1500000L;
+}
 
 // One decoder step for R rows in one launch (decode_rows.hip): position t
 // (< 0: the device step counter's), input tokens cur_tok; ends as
@@ -818,13 +827,13 @@ int run_decoder_rows(mnmt_session* S, int R, int W, bool beam, int t, hipStream_
 // t: run_decoder_rows'.  logits_out: optional [R, V].
 int greedy_step(mnmt_session* S, int R, int t, int stop_at_eos, float* logits_out, hipStream_t s) {
   const mnmt_model* m = S->m;
-  int rc = rows_used(S, R) ? run_decoder_rows(S, R, 1, false, t, s) : run_decoder_layers(S, R, 1, false, s);
+  int rc = rows_used(S, R, false) ? run_decoder_rows(S, R, 1, false, t, s) : run_decoder_layers(S, R, 1, false, s);
   if (rc) return rc;
   const int V = m->info.vocab;
   const int8_t* X;
   int K;
   if ((rc = logits_input(S, R, &X, &K, s))) return rc;
-  if (R <= 8 && !rows_used(S, R)) {
+  if (R <= 8 && !rows_used(S, R, false)) {
     EpiArgs e{EPI_LOGITS_ARGMAX, logits_out, V, 1.f, S->slots};
     LAUNCH(launch_qlinear(X, K, m->E, m->c_out, nullptr, R, K, V, e, s));
   } else {
@@ -1284,7 +1293,7 @@ int embed_step_input(mnmt_session* S, int R, hipStream_t s) {
 int greedy_step_any(mnmt_session* S, int R, int t, int stop_at_eos, float* logits_out, hipStream_t s,
                     bool fold = false, bool last = false, Chain* ch = nullptr) {
   if (step_path_used(S, R)) return greedy_step_v3(S, R, t, stop_at_eos, logits_out, s, fold, last, ch);
-  if (R <= 8 && !factored(S->m) && !rows_used(S, R)) return greedy_step_fused(S, R, t, stop_at_eos, logits_out, s);
+  if (R <= 8 && !factored(S->m) && !rows_used(S, R, false)) return greedy_step_fused(S, R, t, stop_at_eos, logits_out, s);
   return greedy_step(S, R, fold ? t : -1, stop_at_eos, logits_out, s);
 }
 
@@ -1295,8 +1304,8 @@ int beam_step(mnmt_session* S, int R, int W, int t, int steps, hipStream_t s) {
   // factorized embeddings embed their rows in the decoder (the beam update
   // prepares rows of the model width only)
   // (the row-wise decoder embeds its rows too)
-  int rc = rows_used(S, R) ? run_decoder_rows(S, R, W, true, t, s)
-                       : run_decoder_layers(S, R, W, true, s, t > 0 && !factored(m), t);
+  int rc = rows_used(S, R, true) ? run_decoder_rows(S, R, W, true, t, s)
+                                 : run_decoder_layers(S, R, W, true, s, t > 0 && !factored(m), t);
   if (rc) return rc;
   const int d = m->info.d_model, V = m->info.vocab;
   const int8_t* X;
@@ -1316,7 +1325,7 @@ int beam_step(mnmt_session* S, int R, int W, int t, int steps, hipStream_t s) {
   nx.d = d;
   nx.V = V;
   nx.P = m->info.max_pos;
-  nx.steps = factored(m) || rows_used(S, R) ? 0 : steps;
+  nx.steps = factored(m) || rows_used(S, R, true) ? 0 : steps;
   nx.do_ln = !m->info.ln_post;
   nx.g = L0.sa_ln.g;
   nx.b = L0.sa_ln.b;

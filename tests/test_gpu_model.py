@@ -1012,3 +1012,25 @@ def test_row_wise_decoder_many_rows_per_block_beam(torch_dev, i, B, W):
     src, lens = G.make_sources(ROWS[i].vocab, B, (1, 9), seed=328, s_max=9)
     idx = np.unique(np.concatenate([[0, 1, B // 2, B - 1], np.random.default_rng(B).integers(0, B, 12)]))
     _beam_check(torch, dev, ROWS[i], src, lens, W, 5, 0.6, sample=idx)
+
+
+FEW_ROWS = [
+    dataclasses.replace(ROWS[9], name="few-512-2048", w_bits=8), ROWS[9], ROWS[8],
+    dataclasses.replace(ROWS[9], name="few-512-2048-post", w_bits=8, ln_post=1),
+    dataclasses.replace(ROWS[8], name="few-512-1024-post-w4", w_bits=4, ln_post=1), ROWS[6],
+]
+
+
+@pytest.mark.parametrize("cfg", FEW_ROWS, ids=lambda c: c.name)
+def test_few_rows_of_wide_models(torch_dev, cfg):
+    """Rows on both sides of the line between the row-wise decoder and the
+    launches per operator: greedy search of 3, 4 and 5 rows, beam search of one
+    sentence with 2 to 4 hypotheses, widths 384 and 512, both feed-forward
+    ratios, int8 and 4-bit, pre- and post-LN."""
+    torch, dev = torch_dev
+    for B in (3, 4, 5):
+        src, lens = G.make_sources(cfg.vocab, B, (2, 14), seed=330 + B, s_max=14)
+        _greedy_check(torch, dev, cfg, src, lens, 6)
+    for W in (2, 3, 4):
+        src, lens = G.make_sources(cfg.vocab, 1, [11], seed=340 + W, s_max=11)
+        _beam_check(torch, dev, cfg, src, lens, W, 7, 0.6)
