@@ -599,12 +599,21 @@ hipError_t launch_chunk_kc(const int8_t* X, int ldx, const int8_t* W, const floa
   return hipGetLastError();
 }
 
-// K in the fewest chunks of at most 512 bytes, evenly filled.
+// K in the fewest chunks of at most 512 bytes, evenly filled, while every tile
+// has a place at once: a CU's LDS holds two blocks of such chunks, three of 384
+// bytes, eight of 128.  So more tiles take the small chunks (1531 x 512 x 2048,
+// 768 tiles, 7.8 -> 6.0 us; 3000 x 384 x 1152, 846, 6.2 -> 5.6; but 511 x 320 x
+// 4687, 592 tiles and one chunk of K, 8.1 against 7.6), except with a residual,
+// whose rows come ahead under the longer chunks (1811 x 704 x 8671 41 against
+// 46 us).
 template <bool W4>
 hipError_t launch_chunk(const int8_t* X, int ldx, const int8_t* W, const float* scale, const float* bias, int M, int K,
                         int N, const EpiArgs& e, hipStream_t s, int splits = 1) {
   const int kb = K / splits, kc = kb / ((kb + 511) / 512);
-  if (kc <= 128) return launch_chunk_kc<64, 128, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
+  const long blocks = (long)((M + 63) / 64) * ((N + 63) / 64) * splits;
+  const long places = kc == kb && kc <= 384 ? 768 : 512;
+  if (kc <= 128 || (kc > 256 && blocks > places && e.kind != MNMT_EPI_F32_RESID))
+    return launch_chunk_kc<64, 128, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
   if (kc <= 256) return launch_chunk_kc<64, 256, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
   if (kc <= 384) return launch_chunk_kc<64, 384, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
   return launch_chunk_kc<64, 512, W4>(X, ldx, W, scale, bias, M, K, N, e, s, splits);
@@ -907,11 +916,18 @@ hipError_t launch_tiled(const int8_t* X, int ldx, const int8_t* W, const float* 
   // against 28.5 us: this kernel's checked stores read the residual word by word)
   if (resid && K >= 1024 && M % 64 == 0 && N % 128 == 0 && tiles(128, 64) >= kFill)
     return launch_cfg<128, 64, 2, 2, W4>(X, ldx, W, scale, bias, M, K, N, e, s);
-  // few tiles, one chunk of up to 128 bytes (4000 x 64 x 8000 12.4 against
-  // 13.1 us), or residual rows, which only the small tile loads ahead
-  // (2300 x 512 x 2100 14.1 against 20.8 us): 64 x 64; 3000 x 512 x 5001 to
-  // int8 18.4 against 23.2 us the other way
-  if (tiles(128, 64) < kFill || K <= 128 || resid) return launch_chunk<W4>(X, ldx, W, scale, bias, M, K, N, e, s);
+  // 128 x 128 chunk tiles where they are many: fewer leave CUs idle (186 x 1024
+  // x 21849, 342 of them, 13.9 against 12.4 us in 64 x 64; 397 x 512 x 17715, 556,
+  // 11.5 us here), above all when the last row of tiles is mostly empty (131 x
+  // 1856 x 25372, 398, 24 against 21 us, but 1924 x 1664 x 3274, 416, 20.5 here
+  // against 23.5).  One chunk of up to 128 bytes takes 64 x 64 (4000 x 64 x 8000
+  // 12.4 against 13.1 us), but for wide int8 outputs (721 x 64 x 14889 9.3
+  // against 8.5), and so do residual rows, which only the small tile loads ahead
+  // (2300 x 512 x 2100 14.1 against 20.8 us, 291 x 768 x 28301 22 against 27),
+  // unless many of them share a long K (3214 x 832 x 16302 141 against 124 us)
+  const bool many = tiles(128, 128) >= (M >= 512 ? 360 : 448);
+  if (!many || (K <= 128 && !(int8_out && N >= 12000)) || (resid && (K < 768 || M < 1024)))
+    return launch_chunk<W4>(X, ldx, W, scale, bias, M, K, N, e, s);
   return launch_chunk_kc<128, 128, W4>(X, ldx, W, scale, bias, M, K, N, e, s, 1);
 }
 
