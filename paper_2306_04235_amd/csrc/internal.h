@@ -47,7 +47,7 @@ hipError_t launch_qlinear(const int8_t* X, int ldx, const int8_t* W, const float
 
 // The output projection of a batch (logits.hip): Y [M, N] fp32 = (X . W) *
 // scale; W [N, K] row-major or (frag) in fragment order (launch_pack_fragments).
-bool logits_rows_fit(int K, int N);
+bool logits_rows_wins(int M, int K, int N, bool frag);
 hipError_t launch_logits_rows(const int8_t* X, int ldx, const int8_t* W, bool frag, const float* scale, int M, int K,
                               int N, float* Y, hipStream_t s);
 

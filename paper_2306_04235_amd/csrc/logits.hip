@@ -19,6 +19,8 @@
 // and pass through LDS into the matrix operand's order, before X takes the
 // same LDS (gathered straight into that order, 64 bytes of 16 rows per load,
 // they arrive at a quarter of the rate).
+#include <algorithm>
+
 #include "blocks.hpp"
 #include "internal.h"
 
@@ -142,12 +144,29 @@ hipError_t launch_ks(const int8_t* X, int ldx, const int8_t* W, bool frag, const
 
 }  // namespace
 
-// Where it is used: the widths it is compiled for, and vocabularies of more
-// than 24 column blocks (64 to 384 rows of 8000: 3.4-6.0 against 3.8-6.8 us
-// for the tiled GEMM; 512 x 512 x 4096, where 256 blocks of 32 rows would each
-// load 128 KB of weights, 6.8 against 6.5 us).
-bool logits_rows_fit(int K, int N) {
+static bool logits_rows_fit(int K, int N) {
   return (K == 64 || K == 128 || K == 256 || K == 384 || K == 512) && N > 24 * kLgCols;
+}
+
+// Where it is used: the widths it is compiled for, vocabularies of more than 24
+// column blocks, and outputs large enough.  A block's weights (256 columns for
+// the whole K, 128 KB at K = 512) come in before its first product, so a small
+// output waits for them longer than the tiles do (row-major, us, against the
+// faster of the GEMV, fragment and chunk kernels): 3 x 384 x 8000 4.7 against
+// 3.8, 16 x 384 x 8000 4.8 against 3.6, 64 x 512 x 16000 6.1 against 4.3, 256 x
+// 512 x 12000 8.2 against 7.5, 256 x 256 x 16000 6.8 against 7.1, 512 x 512 x
+// 8000 8.5 against 8.7, 1024 x 512 x 32000 31 against 39.  In fragment order
+// they come in sooner: 64 x 256 x 16000 4.1 against 3.8, 128 x 256 x 12000 4.4
+// against 4.5, 256 x 512 x 12000 7.3 against 7.5.  The GEMV of 5 to 8 rows is
+// slower throughout (8 x 64 x 6200 4.6 against 3.1), that of 3 and 4 from 10,000
+// columns on (3 x 384 x 12000 5.0 against 4.8); below 32 rows the tiles store
+// cut-off fragments (16 x 256 x 32000 4.3 against 4.1, in fragment order 3.8).
+bool logits_rows_wins(int M, int K, int N, bool frag) {
+  if (!logits_rows_fit(K, N)) return false;
+  if (M <= 8) return M > 4 || N >= 10000;
+  if (M < 32 && (frag ? N >= (K <= 256 ? 12000 : 20000) : K <= 256 && N >= 20000)) return true;
+  const long out = (long)M * N;
+  return out >= (frag ? 6000L * K : std::min(10000L * K + 600000L, 3600000L));
 }
 
 hipError_t launch_logits_rows(const int8_t* X, int ldx, const int8_t* W, bool frag, const float* scale, int M, int K,

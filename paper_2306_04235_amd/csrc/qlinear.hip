@@ -370,7 +370,7 @@ hipError_t launch_qlinear(const int8_t* X, int ldx, const int8_t* W, const float
                           int K, int N, const EpiArgs& e, hipStream_t s, bool w4) {
   if (M <= 0) return hipSuccess;
   if (w4 && (e.kind == EPI_LOGITS_ARGMAX || K % 64)) return hipErrorInvalidValue;
-  if (!w4 && e.kind == MNMT_EPI_LOGITS && M > 2 && logits_rows_fit(K, N) && e.ldo == N)
+  if (!w4 && e.kind == MNMT_EPI_LOGITS && M > 2 && e.ldo == N && logits_rows_wins(M, K, N, false))
     return launch_logits_rows(X, ldx, W, false, scale, M, K, N, static_cast<float*>(e.out), s);
   if (M <= 8)
     return w4 ? gemv_rows<true>(X, ldx, W, scale, bias, M, K, N, e, s)

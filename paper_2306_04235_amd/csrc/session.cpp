@@ -270,7 +270,7 @@ int logits_input(mnmt_session* S, int R, const int8_t** X, int* K, hipStream_t s
 int project_logits(const mnmt_session* S, const int8_t* X, int K, int R, float* z, hipStream_t s) {
   const mnmt_model* m = S->m;
   const int V = m->info.vocab;
-  if (m->E_frag && K == m->info.d_model && logits_rows_fit(K, V)) {
+  if (m->E_frag && K == m->info.d_model && logits_rows_wins(R, K, V, true)) {
     LAUNCH(launch_logits_rows(X, K, m->E_frag, true, m->c_out, R, K, V, z, s));
   } else {
     const EpiArgs e{MNMT_EPI_LOGITS, z, V, 1.f, nullptr};
