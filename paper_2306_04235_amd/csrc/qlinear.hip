@@ -347,23 +347,41 @@ hipError_t launch_qgemm_split(const int8_t* X, int ldx, const int8_t* W, int M, 
   return launch_gemm_split(X, ldx, W, M, K, N, splits, part, s, w4);
 }
 
-// Where the fragment kernel is the faster one for a plain linear layer.  It
-// loads its operands row by row, 64 bytes of 16 rows at a time, and again in
-// every tile, so the 64 x 64 chunk tiles of gemm.hip pass it as the tiles and K
-// grow: at 64 rows from K = 256 on (64 x 256 x 768 3.2 against 2.8 us, 64 x 512
-// x 30001 18.5 against 4.9; below 64 rows a chunk tile's lower half is stored
-// element by element: 61 x 320 x 5222 3.7 against 4.0 us, 24 x 192 x 19042 3.7
-// against 4.3), in 16 x 16 blocks with their number (128 x 1024 x 1024, 512
-// blocks, 4.2 against 4.6 us; 256 x 256 x 768, 768 blocks, 3.1 against 2.8),
-// from 257 rows with the width (512 x 256 x 256 3.2 against 3.4 us, 512 x 512 x
-// 512 4.2 against 3.4).
-bool small_wins(int M, int K, int N) {
+// Where the fragment kernel is the faster one for a plain linear layer, against
+// the 64 x 64 chunk tiles of gemm.hip.  It gathers 64 bytes of 16 rows per
+// load, again in every tile: cheap while its blocks have a CU each (32 x 32 up
+// to 64 rows, 16 x 16 above), dear past that, and dearer when the rows are a
+// multiple of 128 bytes apart and fall on the same cache channels (64 x 384 x
+// 4000 3.9 us, 64 x 320 x 4000 3.3).  A chunk tile loads whole rows once but
+// stores a fragment that M cuts off element by element, so whole fragments
+// (32 or 64 rows) are its own case.  Measured, fragment against chunk, us:
+//   32, 64 rows: K 128 2.8-4.7 against 2.7-3.1, K 512 4.1-11.8 against 3.4-4.4,
+//     but 64 x 320 x 1001 3.1 against 3.25; with a residual, K 256 3.3 against
+//     3.5, K 512 4.2 against 3.9
+//   other M to 64, a block per CU: 48 x 1024 x 1000 5.9 against 5.0, but 63 x 512
+//     x 2048 4.1 against 4.3, 24 x 512 x 2048 4.0 against 4.1 and 55 x 704 x 91
+//     3.7 against 4.3; past 256 blocks: 9 x 512 x 14000 4.9 against 4.0, 56 x 256 x
+//     8000 4.3 against 3.6, but 20 x 320 x 20000 4.2 against 4.7 and 63 x 320 x
+//     8000 3.8 against 4.2 (logits, stored 16 bytes at a time: 33 x 128 x 6200
+//     3.5 against 3.0); past 512: 56 x 320 x 14000 5.3 against 4.4
+//   65-256 rows: 176 x 512 x 900 (627 blocks) 3.92 against 3.83, 208 x 1024 x
+//     1024 (832) 6.1 against 5.1, but 224 x 320 x 944 3.3 against 3.6 and with a
+//     residual 176 x 512 x 944 4.1 against 4.9, 200 x 768 x 1000 5.7 against 5.2
+//   257-512 rows: 512 x 512 x 512 4.2 against 3.4, 512 x 256 x 256 3.2 against 3.4
+bool small_wins(int M, int K, int N, int kind) {
   if (K > kSmallMaxK || K % 64) return false;
-  if (M < 64 || (K < 256 && qgemm_small_fits(M, K))) return true;
-  if (M == 64) return false;
+  const bool channels = K % 128 == 0, resid = kind == MNMT_EPI_F32_RESID;
+  auto blocks = [&](int t) { return (long)((M + t - 1) / t) * ((N + t - 1) / t); };
+  if (M <= 64) {
+    if (M % 32 == 0) return K < (resid ? 512 : 128) || (!channels && blocks(32) <= 256);
+    if (M > 32 && kind == MNMT_EPI_LOGITS && blocks(32) > 256) return false;
+    if (blocks(32) > 512) return M > 32 ? K < (channels ? 128 : 256) : K < 256 || !channels;
+    if (blocks(32) > 256) return K < 256 || !channels;
+    return M <= 32 || K < 768 || !channels;
+  }
   if (!qgemm_rows_fit(M, K, N)) return false;
-  if (K < 256) return true;
-  return M <= 256 ? (M + 15) / 16 * ((N + 15) / 16) <= 640 : N <= 256;
+  if (K < 256 || !channels) return true;
+  return M <= 256 ? blocks(16) <= 640 || (resid && K < 768) : N <= 256;
 }
 
 hipError_t launch_qlinear(const int8_t* X, int ldx, const int8_t* W, const float* scale, const float* bias, int M,
@@ -376,7 +394,7 @@ hipError_t launch_qlinear(const int8_t* X, int ldx, const int8_t* W, const float
     return w4 ? gemv_rows<true>(X, ldx, W, scale, bias, M, K, N, e, s)
               : gemv_rows<false>(X, ldx, W, scale, bias, M, K, N, e, s);
   if (e.kind == EPI_LOGITS_ARGMAX) return hipErrorInvalidValue;  // arg-max fusion is a batch-1 path
-  if (small_wins(M, K, N))
+  if (small_wins(M, K, N, e.kind))
     return launch_qgemm_small(nullptr, X, ldx, W, scale, bias, M, K, N, e, s, w4);
   return launch_gemm(X, ldx, W, scale, bias, M, K, N, e, s, w4);
 }

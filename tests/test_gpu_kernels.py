@@ -188,6 +188,11 @@ def test_qlinear_wide_logits(torch_dev, M, K, N):
     (1501, 192, 2911, 8), (2111, 448, 2083, 4),  # 128 x 128 tiles
     (1985, 1024, 8197, 8), (2048, 256, 8193, 8),  # 256 x 128 slab tiles (the second: the wide outputs)
     (4096, 1024, 1024, 8),  # 128 x 64 slab tiles (the residual)
+    (1531, 512, 1537, 8), (1000, 448, 2111, 4),  # more than 512 tiles of 64 x 64: chunks of 128
+    (555, 384, 4097, 8),  # 585 tiles: one chunk of 384
+    (32, 128, 1001, 8), (63, 1024, 1031, 4), (28, 512, 14003, 8), (57, 320, 16417, 8),  # chunk tiles of few rows
+    (40, 256, 8001, 4), (20, 320, 14003, 8),  # past 256 blocks, chunk tiles and fragments
+    (1025, 768, 5001, 8),  # 128 x 128 tiles with a residual over a long K
 ], ids=lambda v: str(v))
 def test_qlinear_tiles_unaligned(torch_dev, M, K, N, bits):
     """Tiles cut off by M and N, chunks of K that are not full, rows of no
