@@ -1034,3 +1034,51 @@ def test_few_rows_of_wide_models(torch_dev, cfg):
     for W in (2, 3, 4):
         src, lens = G.make_sources(cfg.vocab, 1, [11], seed=340 + W, s_max=11)
         _beam_check(torch, dev, cfg, src, lens, W, 7, 0.6)
+
+
+# shapes the row-wise kernels do not take (feed-forward neither 2 nor 4 times
+# the width), which run operator by operator
+OPER_128 = G.ModelConfig("oper-128", 128, 4, 384, 2, 3, 700, ln_post=0, seed=351, random_gamma=True, weight_std=0.1)
+OPER_64_POST = G.ModelConfig("oper-64-post", 64, 4, 192, 2, 2, 300, ln_post=1, seed=352, random_gamma=True,
+                             weight_std=0.1)
+OPER_512 = G.ModelConfig("oper-512", 512, 8, 1536, 2, 2, 300, ln_post=0, seed=353, random_gamma=True, weight_std=0.05)
+
+
+def _w4(cfg):
+    return dataclasses.replace(cfg, name=cfg.name + "-w4", w_bits=4)
+
+
+@pytest.mark.parametrize("cfg", [OPER, OPER_128, _w4(OPER), _w4(OPER_128)], ids=lambda c: c.name)
+def test_operator_path_layernorm_forms(torch_dev, monkeypatch, cfg):
+    """Pre-LN beam search above 64 rows, operator by operator, at widths 128
+    and 256: the LayerNorms in the prologue of the kernels they feed and, with
+    MNMT_LN_FUSED=0, as kernels of their own; the self-attention computing its
+    rows' Q/K/V and, with MNMT_QKV_FUSED=0, the projection as a GEMM; 2 to 8
+    hypotheses, up to 128 and 256 target positions; 4-bit weights read
+    packed."""
+    from paper_2306_04235_amd import mnmt
+
+    torch, dev = torch_dev
+    flags = mnmt.LOAD_PACKED_4BIT_ONLY if cfg.w_bits == 4 else 0
+    src, lens = G.make_sources(cfg.vocab, 19, (2, 24), seed=354, s_max=24)
+    for ln, qkv in (("1", "1"), ("0", "1"), ("1", "0")):
+        monkeypatch.setenv("MNMT_LN_FUSED", ln)
+        monkeypatch.setenv("MNMT_QKV_FUSED", qkv)
+        _beam_check(torch, dev, cfg, src, lens, 4, 12, 0.6, parallel=True, flags=flags)
+    monkeypatch.setenv("MNMT_QKV_FUSED", "1")
+    for B, W in ((9, 8), (40, 2)):
+        src, lens = G.make_sources(cfg.vocab, B, (2, 24), seed=355 + W, s_max=24)
+        _beam_check(torch, dev, cfg, src, lens, W, 8, 0.6, parallel=True, flags=flags)
+    src, lens = G.make_sources(cfg.vocab, 17, (1, 40), seed=364, s_max=40)
+    for steps in (100, 140):
+        _beam_check(torch, dev, cfg, src, lens, 4, steps, 0.6, sample=range(0, 17, 4), parallel=True, flags=flags)
+
+
+@pytest.mark.parametrize("cfg", [OPER, OPER_128, OPER_64_POST, OPER_512, _w4(OPER)], ids=lambda c: c.name)
+def test_operator_path_greedy(torch_dev, cfg):
+    """Greedy search operator by operator: 3 to 8 rows (the LayerNorm in the
+    GEMV), 12 rows (the matrix cores), and the encoder above 64 rows."""
+    torch, dev = torch_dev
+    for B in (3, 5, 8, 12):
+        src, lens = G.make_sources(cfg.vocab, B, (2, 30), seed=370 + B, s_max=30)
+        _greedy_check(torch, dev, cfg, src, lens, 7)
