@@ -265,7 +265,9 @@ int mnmt_session_tensor(const mnmt_session* session, const char* name, void** d_
  * the arg-max epilogues), d_Y [M, N] of the epilogue's type.  K must be a positive multiple
  * of 64 and at most 8192; M >= 0, N >= 1.  M <= 8 runs the wavefront
  * reduction kernel (the arg-max epilogue at M <= 2, K <= 512: the decoder's
- * logits kernel on the matrix cores), larger M the i8 matrix-core kernels. */
+ * logits kernel on the matrix cores; MNMT_EPI_LOGITS of int8 weights at 3 rows
+ * and more over wide vocabularies: the batched logits kernel, on them too),
+ * larger M the i8 matrix-core kernels. */
 int mnmt_qlinear(const int8_t* d_X, const int8_t* d_W, const float* d_scale, const float* d_bias,
                  int M, int K, int N, int epilogue, float gamma, void* d_Y, void* stream);
 

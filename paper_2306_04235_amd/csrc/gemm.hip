@@ -1,5 +1,5 @@
-// gemm.hip -- int8 GEMM with fused epilogues for more than 64 rows (the
-// batched encoder, beam decoding and the quantized-linear sweep), on the i8
+// gemm.hip -- int8 GEMM with fused epilogues for more than 8 rows (where the
+// fragment kernel of qlinear.hip is not the faster one: small_wins), on the i8
 // matrix cores: Y[m, n] = epilogue(sum_k X[m, k] W[n, k]) (Section 4.1's 8-bit
 // GEMM; the epilogues of Section 4.2 applied as the tile is written).
 //

@@ -1,8 +1,8 @@
 // logits.hip -- the output projection of a batch: Y[m, n] = (X[m] . W[n]) *
 // scale[n] in fp32 over a wide vocabulary (K = 64 KS up to 512, any M).
 //
-// Bound by its own output: 65.5 MB for 512 rows of 32,000 logits, 12 us at the
-// 5.5 TB/s that plain stores reach, against 3.4 us of matrix-core time.  So a
+// Bound by its own output: 65.5 MB for 512 rows of 32,000 logits, 10.6 us at the
+// 6.2 TB/s that a plain write kernel reaches, against 3.4 us of matrix-core time.  So a
 // block does all of its loading at its start, and then only multiplies and
 // stores: each of its 8 waves keeps the weights of 32 columns for the whole K
 // in registers (two tiles of 16, 64 VGPRs at K = 512), the block's rows (up to
@@ -11,8 +11,10 @@
 // loads wait behind stores: one in-order counter).  X is the A operand, so 16
 // lanes store 64 contiguous bytes of a row (with the weights there a lane
 // stores 16 bytes of its own row, four times the store requests: 10.2 against
-// 9.3 us at 256 x 256 x 32000).  256 x 256 x 32000: 12.6 -> 9.6 us, 512 x 512 x
-// 32000: 27.5 -> 19.5 us, 4 x 256 x 32000: 7.8 -> 3.8 us.
+// 9.3 us at 256 x 256 x 32000).  Against the tiled kernels of the time, and the
+// GEMV for 4 rows (row-major; in fragment order): 256 x 256 x 32000 12.6 -> 9.7
+// us (9.1), 512 x 512 x 32000 27.5 -> 17.7 us (17.1), 4 x 256 x 32000 7.8 -> 4.0
+// us (3.6).
 //
 // FRAG: W is in fragment order (launch_pack_fragments), each load one
 // contiguous kilobyte.  Row-major, the block's weights come in as whole rows

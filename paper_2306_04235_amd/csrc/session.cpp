@@ -552,8 +552,9 @@ hipError_t pack_encoder(const mnmt_model* m, const std::vector<int32_t>& num, in
   return e;
 }
 
-// Encoder over the session's current batch (rows = B * S, padded rows are
-// computed and ignored), then every decoder layer's cross keys/values.
+// Encoder over the session's current batch (rows = B * S; padded rows are
+// ignored, and the row-wise encoder leaves blocks of them out), then every
+// decoder layer's cross keys/values.
 int run_encoder(mnmt_session* S, hipStream_t s) {
   const mnmt_model* m = S->m;
   const int d = m->info.d_model, rows = S->B * S->S;

@@ -124,8 +124,8 @@ W4_SHAPES = [(1, 256, 1024), (2, 2048, 77), (4, 1024, 256), (7, 64, 33), (33, 19
 def test_qlinear_4bit_weights(torch_dev, M, K, N):
     """4-bit weights (W-E-A 4-8-8) read packed by every quantized-linear path:
     the wavefront-reduction GEMV (M <= 8), the one-round-trip matrix-core
-    kernel (its 32x32 and one-wave 16x16 blocks), the slab-pipelined GEMM and
-    the persistent GEMM (the last two shapes).  The codes in [-7, 7] are packed
+    kernel (its 32x32 and one-wave 16x16 blocks), the chunk tiles and the
+    persistent GEMM (the last two shapes).  The codes in [-7, 7] are packed
     as the model file stores them; the int32 sums and every epilogue equal the
     oracle's on the codes."""
     torch, dev = torch_dev

@@ -392,7 +392,10 @@ SPLIT_BEAM = G.ModelConfig("split-preln-beam", 128, 4, 2048, 2, 3, 700, ln_post=
 @pytest.mark.parametrize("cfg", [DIVERSE, VARIED_BEAM, SPLIT_BEAM], ids=lambda c: c.name)
 def test_batched_layernorm_forms(torch_dev, monkeypatch, cfg):
     """Pre-LN beam search above 64 rows (19 sentences of beam 4: 76 rows, a
-    ragged last tile of 16 rows): the LayerNorms in the prologue of the
+    ragged last tile of 16 rows).  The first two models run the row-wise
+    decoder, which the switches below do not touch: its widths, lengths and
+    hypotheses.  The third runs operator by operator (as the models of
+    test_operator_path_layernorm_forms): the LayerNorms in the prologue of the
     kernels they feed (each block of the one-round-trip GEMM normalizes its
     rows) and, with MNMT_LN_FUSED=0 (read at session creation), as kernels of
     their own; the self-attention computing its rows' Q/K/V and, with
@@ -434,9 +437,9 @@ DIVERSE_EOS = dataclasses.replace(DIVERSE, name="diverse-eos", eos_gain=4.0)
 def test_end_of_sentence_search(torch_dev):
     """Beam search and greedy search with stop_at_eos on models that emit EOS
     at varied steps (the oracle's lengths range from 1 to the maximum):
-    batched beam above and below 64 rows (the fused and the general batched
-    decoder), small-model beam at widths 2, 4, 6, and greedy at 1, 2 and 5
-    rows (the chained batch-1 step, the 2-row and the 3-8-row paths)."""
+    batched beam above and below 64 rows, small-model beam at widths 2, 4, 6
+    (all in the row-wise decoder), and greedy at 1, 2 and 5 rows (the chained
+    batch-1 step, the 2-row step and the row-wise decoder)."""
     torch, dev = torch_dev
     src, lens = G.make_sources(VARIED_EOS.vocab, 19, (2, 24), seed=97, s_max=24)
     for W in (4, 2):
@@ -460,11 +463,11 @@ HEAD128 = G.ModelConfig("head-128", 256, 2, 512, 1, 1, 600, ln_post=1, seed=89, 
 
 @pytest.mark.parametrize("cfg", [HEAD16, HEAD128], ids=lambda c: c.name)
 def test_attention_length_and_head_classes(torch_dev, cfg):
-    """The batched attention kernels' length classes (64, 128, 256 keys) and
-    head-width classes (16-64 and 128) against the oracle, up to the maximum
-    lengths (256 source tokens, 256 target positions): greedy at 3 rows
-    (batched encoder, 3-8-row decoder) and beam search at 8 rows, with a
-    one-token source among long ones."""
+    """Attention over 64, 128 and 256 keys against the oracle, up to the maximum
+    lengths (256 source tokens, 256 target positions), in the row-wise kernels
+    (heads of 16) and operator by operator (heads of 128, whose length classes
+    these are): greedy at 3 rows and beam search at 8 rows, with a one-token
+    source among long ones."""
     torch, dev = torch_dev
     src, lens = G.make_sources(cfg.vocab, 3, [256, 131, 1], seed=90, s_max=256)
     _greedy_check(torch, dev, cfg, src, lens, 200, check_logits=False)
@@ -476,10 +479,10 @@ def test_attention_length_and_head_classes(torch_dev, cfg):
 
 def test_postln_beam_above_64_rows(torch_dev):
     """Post-LN beam search above 64 rows (the normalized rows replace the
-    residual stream, so the batched decoder keeps its LayerNorm kernels):
-    76 rows of a d-64 model on the one-wave 16x16 GEMM blocks, and 68 rows
-    of a d-256 model with 128-wide heads, whose cross-attention computes its
-    query rows itself, against the oracle on every sentence."""
+    residual stream): 76 rows of a d-64 model in the row-wise decoder, and 68
+    rows of a d-256 model with 128-wide heads, operator by operator (LayerNorm
+    kernels, and a cross-attention that computes its query rows itself),
+    against the oracle on every sentence."""
     torch, dev = torch_dev
     src, lens = G.make_sources(SMALL_POST.vocab, 19, (2, 24), seed=99, s_max=24)
     _beam_check(torch, dev, SMALL_POST, src, lens, 4, 12, 0.6, parallel=True)
@@ -626,11 +629,11 @@ def test_4bit_packed_only_models(torch_dev):
 
 def test_4bit_packed_only_batched_paths(torch_dev):
     """Packed-only 4-bit models on the batched paths, which then read the
-    packed rows too: 3-row greedy steps (the fused GEMV), beam search on a
-    small model, and the mobile beam workload (64 sentences of 10-60 tokens:
-    the encoder's 3840-row projections on the tiled GEMM, the 256-row beam
-    decoder on the one-wave matrix-core blocks), a dozen sentences of it
-    against the oracle, shortest and longest included."""
+    packed codes too (the row-wise kernels a copy of them in fragment order,
+    the cross keys' and values' projections the rows): 3-row greedy steps,
+    beam search on a small model, and the mobile beam workload (64 sentences
+    of 10-60 tokens), a dozen sentences of it against the oracle, shortest and
+    longest included."""
     from paper_2306_04235_amd import mnmt
 
     torch, dev = torch_dev
@@ -641,7 +644,7 @@ def test_4bit_packed_only_batched_paths(torch_dev):
     _beam_check(torch, dev, div4, src, lens, 2, 8, 0.6, flags=flags)
     src, lens = G.make_sources(div4.vocab, 12, [9, 5, 7, 16, 3, 11, 8, 8, 2, 16, 12, 6], seed=32, s_max=16)
     _greedy_check(torch, dev, div4, src, lens, 6, flags=flags)
-    # above 64 rows at d 128: the fused self-attention on packed W_qkv rows
+    # above 64 rows at d 128
     src, lens = G.make_sources(div4.vocab, 19, (2, 16), seed=34, s_max=16)
     _beam_check(torch, dev, div4, src, lens, 4, 10, 0.6, parallel=True, flags=flags)
     mob4 = dataclasses.replace(G.MOBILE, name="mobile-w4", w_bits=4)
@@ -685,8 +688,7 @@ SHARED_256 = G.ModelConfig("shared-256", 256, 4, 1024, 6, 2, 32000, ln_post=0, s
 def test_cross_layer_sharing_models(torch_dev):
     """Cross-layer parameter sharing (Section 2.2): layers that reuse another
     layer's parameters (aliased device pointers, stored once) on every path --
-    the batch-1 chained step and encoder, the 3-8 row and matrix-core paths,
-    beam search -- against the oracle."""
+    the batch-1 chained step and encoder, the row-wise kernels, beam search -- against the oracle."""
     torch, dev = torch_dev
     for B in (1, 2, 5, 12):
         src, lens = G.make_sources(SHARED.vocab, B, (3, 12), seed=60 + B, s_max=12)
@@ -707,8 +709,9 @@ def test_factorized_embedding_models(torch_dev):
     """Embedding factorization (Section 2.1): rows of width E projected to the
     model width on the way in (k_embed_proj) and the final rows projected back
     (an int8 linear layer over the transposed matrix) before the tied logits,
-    on the general greedy path at 1, 5 and 12 rows (per-step logits bits via
-    mnmt_decode_step) and in beam search, against the oracle."""
+    in greedy search of 1 row (operator by operator), 5 and 12 rows (the
+    row-wise decoder; per-step logits bits via mnmt_decode_step) and in beam
+    search, against the oracle."""
     torch, dev = torch_dev
     for cfg in (FACTOR, FACTOR_POST):
         om, gm = _pair(cfg)
