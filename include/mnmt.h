@@ -192,10 +192,10 @@ int mnmt_session_bytes(const mnmt_model* model, const mnmt_session_cfg* cfg, siz
  * row-wise kernels: the decoder's if max_batch * beam is 3 or more, the
  * encoder's if max_batch * max_src_len is more than 64, of models with d_model
  * 64, 128, 256, 384 or 512, d_ffn 2 or 4 times it and heads of at most 64),
- * and returns when that is done.  It waits for
- * no other stream, so every earlier use of the workspace's memory must have
- * finished before the call: memory from an allocator that reuses blocks in
- * stream order needs that stream synchronized first. */
+ * and returns when that is done.  It waits for no other stream, so every
+ * earlier use of the workspace's memory must have finished before the call:
+ * memory from an allocator that reuses blocks in stream order needs that
+ * stream synchronized first. */
 int mnmt_session_create(const mnmt_model* model, const mnmt_session_cfg* cfg, void* d_ws,
                         size_t ws_bytes, mnmt_session** out);
 void mnmt_session_free(mnmt_session* session);
@@ -213,14 +213,14 @@ int mnmt_encode(mnmt_session* session, const int32_t* d_src, const int32_t* d_le
  * the previous step's outputs), output d_next [B] = arg max of the logits
  * (smallest id among equal maxima), optional d_logits [B, V] fp32.  The step
  * index lives in device memory, so a call captured into a graph decodes the
- * next position at each replay; except for 1-2 rows, and for 3-8 rows of a
- * model the row-wise decoder does not take (see mnmt_session_create), whose
- * launches also carry the position the host counted.  Errors: MNMT_E_CAPACITY
- * past max_tgt_len (the library counts its calls; replays are the caller's to
- * count);
- * MNMT_E_UNSUPPORTED on a session created with beam > 1 (beam search keeps
- * its hypotheses, parents and finished list across steps and runs only as a
- * whole search through mnmt_translate). */
+ * next position at each replay; except for 1-2 rows, and for 3-8 rows outside
+ * the row-wise decoder (models it does not take, see mnmt_session_create, and
+ * 3 or 4 rows of wide ones), whose launches also carry the position the host
+ * counted.  Errors: MNMT_E_CAPACITY past max_tgt_len (the library counts its
+ * calls; replays are the caller's to count); MNMT_E_UNSUPPORTED on a session
+ * created with beam > 1 (beam search keeps its hypotheses, parents and
+ * finished list across steps and runs only as a whole search through
+ * mnmt_translate). */
 int mnmt_decode_step(mnmt_session* session, const int32_t* d_prev, int32_t* d_next, float* d_logits,
                      void* stream);
 
